@@ -28,6 +28,7 @@ using namespace dtk;
 namespace {
 
 constexpr uint32_t DEFAULT_ROUND_MAX = 1u << 20;
+static_assert(DEFAULT_ROUND_MAX <= 1u << CLAIM_PLACE_BITS, "a place in the list fits a claim stamp");
 constexpr uint32_t DEFAULT_CAVITY_CAP = 128;
 constexpr uint32_t DEFAULT_LANES = 16;
 constexpr double DEFAULT_ROUND_FRACTION = 1.0 / 16.0;
@@ -125,6 +126,7 @@ struct dt_ctx {
     bool exact_needed = false;
     unsigned long long deferred_base = 0;
     uint32_t large_lanes = 256;  // the same in rounds for large cavities (64 or 256)
+    uint32_t rank_shift = 0;  // ranks of the call's points >> rank_shift fit a claim stamp
     double frac = 0;     // round size as a fraction of the mesh's vertices
     bool frac_auto = true;  // round_fraction 0: short rounds take SHORT_ROUND_FRACTION_SCALE times more
     uint32_t call_clouds = 1;  // clouds of the insertion call in progress
@@ -137,6 +139,7 @@ struct dt_ctx {
         double ms = 0;
     } tuned[64];
     uint32_t *defer = nullptr;             // candidates handed to the exact-predicate pass
+    uint32_t *lost = nullptr;              // attempts one of whose claims was displaced
     void *cav = nullptr, *outc = nullptr;  // adjacency codes (4 or 8 bytes each)
     uint32_t *bnd = nullptr, *cnt = nullptr;
     uint4 *scr_v = nullptr;
@@ -383,8 +386,8 @@ int ensure_round_buffers(dt_ctx *c, uint32_t rmax) {
         c->lpt[k] = c->lrank[k] = nullptr;
     }
     dev_free(c, c->cav); dev_free(c, c->bnd); dev_free(c, c->outc); dev_free(c, c->cnt); dev_free(c, c->status);
-    dev_free(c, c->scr_v); dev_free(c, c->scr_n); dev_free(c, c->defer);
-    c->defer = nullptr;
+    dev_free(c, c->scr_v); dev_free(c, c->scr_n); dev_free(c, c->defer); dev_free(c, c->lost);
+    c->defer = c->lost = nullptr;
     c->scr_v = nullptr;
     c->scr_n = nullptr;
     c->cav = c->outc = nullptr;
@@ -405,6 +408,7 @@ int ensure_round_buffers(dt_ctx *c, uint32_t rmax) {
          dev_alloc(c, (void **)&c->cnt, 2 * (size_t)rmax * sizeof(uint32_t)) == hipSuccess &&
          dev_alloc(c, (void **)&c->status, rmax) == hipSuccess &&
          dev_alloc(c, (void **)&c->defer, rmax * sizeof(uint32_t)) == hipSuccess &&
+         dev_alloc(c, (void **)&c->lost, rmax * sizeof(uint32_t)) == hipSuccess &&
          dev_alloc(c, (void **)&c->scr_v, c->bufC * sizeof(uint4)) == hipSuccess &&
          dev_alloc(c, &c->scr_n, c->bufC * 4 * cb) == hipSuccess;
     c->buf_wide = c->wide;
@@ -413,6 +417,7 @@ int ensure_round_buffers(dt_ctx *c, uint32_t rmax) {
         c->list_cap = 0;
         return fail(c, DT_E_CAPACITY, "round buffers for %u insertions do not fit", rmax);
     }
+    HIPCHK(hipMemsetAsync(c->lost, 0, rmax * sizeof(uint32_t), c->stream));  // no round's mark is 0
     return DT_OK;
 }
 
@@ -566,6 +571,7 @@ int enqueue_round(dt_ctx *c, int ci, int ni, int oi, uint32_t max_cand, uint32_t
     a.outc = c->outc;
     a.cnt = c->cnt;
     a.status = c->status;
+    a.lost = c->lost;
     a.fl_cur = c->fl[c->fl_idx];
     a.fl_next = c->fl[c->fl_idx ^ 1];
     a.flcap = c->flcap;
@@ -579,13 +585,19 @@ int enqueue_round(dt_ctx *c, int ci, int ni, int oi, uint32_t max_cand, uint32_t
     // candidate's 16 capC bytes of ball scratch (4-byte entries, or 8-byte with 64-bit codes)
     a.hmg = 1u << (31 - __builtin_clz(std::min<uint32_t>((c->wide ? 2u : 4u) * std::min<uint32_t>(capC, 1u << 24),
                                                          1u << 30)));
-    // Claim words are never reset between rounds: later rounds stamp lower.  When the low 32
-    // bits of the round counter wrap, every claim left in the pool would outrank the new
+    // Claim words are not reset between rounds: later rounds stamp lower.  When the stamps'
+    // bits of the round counter wrap, every claim left in the pool would come before the new
     // stamps, so the claim words are reset to the empty value first (the kernels of earlier
-    // rounds are ahead of the reset on the same stream).
-    if ((c->round_counter & 0xFFFFFFFFull) == 0 && c->round_counter != 0 && c->tcap)
+    // rounds are ahead of the reset on the same stream).  The marks of lost attempts hold 31
+    // bits of the counter and are cleared when those wrap.
+    constexpr uint64_t ROUNDS = 1ull << CLAIM_ROUND_BITS;
+    if (c->round_counter % ROUNDS == 0 && c->round_counter != 0 && c->tcap)
         HIPCHK(launch_reset_claims(c->T, c->wide, c->tcap, c->stream));
-    a.round_hi = (0xFFFFFFFFull - (c->round_counter & 0xFFFFFFFFull)) << 32;
+    if ((c->round_counter & 0x7FFFFFFFull) == 0 && c->round_counter != 0)
+        HIPCHK(hipMemsetAsync(c->lost, 0, c->list_cap * sizeof(uint32_t), c->stream));
+    a.round_hi = (ROUNDS - 1 - c->round_counter % ROUNDS) << CLAIM_ROUND_SHIFT;
+    a.lost_mark = (uint32_t)c->round_counter | 0x80000000u;
+    a.rank_shift = c->rank_shift;
     a.clk = nullptr;
     if (c->trace >= 2 && max_cand) {
         if (c->clk_cap[slot] < max_cand) {
@@ -889,6 +901,8 @@ int run_rounds(dt_ctx *c, const Levels &lv, const uint32_t *d_start, const uint3
                const uint32_t *d_bits, const unsigned long long *d_rank_base, uint64_t base, uint64_t n) {
     const uint32_t rmax = c->list_cap;
     const double frac = c->frac;
+    c->rank_shift = 0;
+    while ((lv.total_ranks >> c->rank_shift) >> CLAIM_RANK_BITS) ++c->rank_shift;
     uint64_t next_rank = 0;
     uint64_t rounds_this_call = 0;
     int fly = -1;            // snapshot slot of the round in flight, or -1
@@ -1867,7 +1881,7 @@ int dt_destroy(dt_ctx *c) {
     for (int k = 0; k < 3; ++k) f(c->clk[k]);
     for (int k = 0; k < 4; ++k) { f(c->lpt[k]); f(c->lrank[k]); }
     f(c->cav); f(c->bnd); f(c->outc); f(c->cnt); f(c->status);
-    f(c->scr_v); f(c->scr_n); f(c->defer);
+    f(c->scr_v); f(c->scr_n); f(c->defer); f(c->lost);
     f(c->ctr);
     f(c->stat);
     if (c->hring) hipHostFree(c->hring);

@@ -7,13 +7,17 @@
 //              search by perturbed insphere, ghosts by the half-space + circumdisk rule of
 //              Sec. 2.6), by a group of lanes per insertion.  The attempt claims every
 //              tetrahedron it touches, once it has tested it, with atomicMin on the
-//              tetrahedron's 64-bit claim word: its stamp S = (round part, 2 rank) for cavity
+//              tetrahedron's 64-bit claim word: its stamp S (see claim_stamp) for cavity
 //              tetrahedra, S + 1 for tetrahedra found outside.  Meeting a lower claim that
-//              excludes it ends the attempt (one search step later).
-//   k_ball   : an attempt wins iff no lower attempt claimed a tetrahedron of its cavity
-//              (either way) or has one of its outer tetrahedra in its cavity, so the cavities
-//              of winners are disjoint from each other and from each other's adjacent
-//              tetrahedra (rules 1a-1c and 2 of Sec. 3.2); the lowest rank in a
+//              excludes it ends the attempt (one search step later); displacing the cavity
+//              claim of a later attempt marks that attempt as lost.
+//   k_ball   : an attempt wins iff it completed its cavity and nobody marked it.  If two
+//              attempts share a cavity tetrahedron, or one's cavity touches the other's outer
+//              tetrahedra, the later one has lost: some tetrahedron of its cavity is claimed
+//              by the earlier one too (adjacency runs both ways), and on that word either it
+//              found a lower claim itself or its claim was displaced by a lower one.  So the
+//              cavities of winners are disjoint from each other and from each other's adjacent
+//              tetrahedra (rules 1a-1c and 2 of Sec. 3.2); the first in the order of a
 //              round always wins, so every round makes progress.  A winner builds
 //              DelaunayBall (Sec. 2.5): one tetrahedron per boundary facet, glued a priori to
 //              the outer tetrahedron, and glued to its three sibling tetrahedra through an
@@ -331,6 +335,28 @@ __device__ __forceinline__ int tet_inside(const typename K::Rec *T, const Vert *
 
 // ------------------------------------------------------------------ walk + cavity + claim
 
+// Stamp of candidate i: the round (later rounds are lower), the leading bits of its rank
+// (insertions that have waited longer come first, and neighbours on the curve differ at once,
+// the ranks being bit-reversed positions), its place in the list, which names the owner of a
+// claim found in the pool, and a zero for a cavity claim (one for an outer claim).
+__device__ __forceinline__ unsigned long long claim_stamp(const RoundArgs &a, uint32_t i) {
+    return a.round_hi | ((unsigned long long)(a.cand_rank[i] >> a.rank_shift) << (CLAIM_PLACE_BITS + 1)) |
+           ((unsigned long long)i << 1);
+}
+__device__ __forceinline__ uint32_t claim_owner(unsigned long long stamp) {
+    return (uint32_t)(stamp >> 1) & ((1u << CLAIM_PLACE_BITS) - 1u);
+}
+
+// The value an attempt's claim (stamp S; `inside`: on a tetrahedron of its cavity) found in the
+// claim word: true if it loses the attempt.  A cavity claim of this round that the claim
+// displaced loses its own attempt, which is marked.
+__device__ __forceinline__ bool settle_claim(const RoundArgs &a, unsigned long long S, bool inside,
+                                             unsigned long long found) {
+    if (found > S && !(found & 1ull) && (found ^ S) >> CLAIM_ROUND_SHIFT == 0)
+        a.lost[claim_owner(found)] = a.lost_mark;
+    return found < S && (inside || !(found & 1ull));
+}
+
 // Sizes of the cavity kernel's per-insertion state: a queue of CAPL cavity tetrahedra and a
 // set of HM entries holding the attempt's own cavity and outer tetrahedra.  Regular rounds
 // keep both in LDS at (128, 256) with 4 to 64 lanes per insertion; rounds for large
@@ -399,9 +425,12 @@ __device__ __forceinline__ void lane_fence() {
 // through), which is skipped when the tetrahedron is expanded.
 //
 // Claims: every neighbour examined is tested first and then claimed once, with S if it is
-// inside (S is the attempt's stamp: round, then rank) and S + 1 if it is outside.  A lower
-// value returned on an inside tetrahedron, or a lower even value (a lower attempt's cavity)
-// on an outside one, loses the attempt.  The attempt's own tetrahedra are tracked in the
+// inside (S is the attempt's stamp) and S + 1 if it is outside; settle_claim takes what the
+// claim found one step later, when the next loads are in flight.  The claims on tetrahedra
+// outside are needed: without them an attempt that has lost runs on and displaces others
+// (measured: 8 % more rounds at 1e5 points; a plain load of the claim word in their place saved
+// 6 % of this kernel at 1e7 but then winners must read all the words of their cavities and
+// neighbours again).  The attempt's own tetrahedra are tracked in the
 // set, so each is claimed and tested once.  GLOBAL keeps queue and set in global memory
 // (any capC).
 //
@@ -434,7 +463,7 @@ __global__ __launch_bounds__(256) void k_cavity_g(RoundArgs a) {
         const uint32_t i = DEFER ? a.defer[j] : j;
         uint8_t status = ST_NONE;
         const uint32_t p = a.cand_pt[i];
-        const unsigned long long S = a.round_hi | (2ull * a.cand_rank[i]);
+        const unsigned long long S = claim_stamp(a, i);
         const Vert pv = a.V[p];
         const P3 P = {pv.x, pv.y, pv.z};
         const bool clocked = !FULL && !DEFER && a.clk != nullptr;
@@ -553,9 +582,9 @@ __global__ __launch_bounds__(256) void k_cavity_g(RoundArgs a) {
             // = (gl / 4, gl % 4).
             for (uint32_t h = gl; h < hms; h += GS) mem[h] = mem_empty<E>();
             lane_fence<GLOBAL>();
-            // each step's claims are checked at the next step (or after the last), once that
+            // each step's claims are settled at the next step (or after the last), once that
             // step's loads are in flight, so that the atomics' latency overlaps them; the
-            // walk's tetrahedron is inside, its claim is checked with the first step's
+            // walk's tetrahedron is inside, its claim is settled with the first step's
             bool pneed = gl == 0, pinside = true;
             unsigned long long po1 = ~0ull;
             if (gl == 0) {
@@ -591,9 +620,10 @@ __global__ __launch_bounds__(256) void k_cavity_g(RoundArgs a) {
                     cv = T[c].v;
                     cn = T[c].n;
                 }
-                // the previous step's claims: a lower claim on a tetrahedron of this cavity,
-                // or a lower cavity claim (even) on one outside it, loses the attempt
-                if (__ballot(pneed && po1 < S && (pinside || !(po1 & 1ull))) & gmask) {
+                // the previous step's claims
+                const bool beaten = pneed && settle_claim(a, S, pinside, po1);
+                pneed = false;
+                if (__ballot(beaten) & gmask) {
                     status = ST_CONFLICT;
                     break;
                 }
@@ -665,6 +695,9 @@ __global__ __launch_bounds__(256) void k_cavity_g(RoundArgs a) {
                 const unsigned long long mi = __ballot(first_in) & gmask;
                 const unsigned long long mo = __ballot(outside) & gmask;
                 const uint32_t ni = (uint32_t)__popcll(mi), no = (uint32_t)__popcll(mo);
+                pneed = need;
+                pinside = inside;
+                po1 = o1;
                 if (ncav + ni > capL || nbnd + no > capF || (__ballot(ins < 0) & gmask)) {
                     status = ST_OVERFLOW;
                     break;
@@ -682,13 +715,12 @@ __global__ __launch_bounds__(256) void k_cavity_g(RoundArgs a) {
                 }
                 ncav += ni;
                 nbnd += no;
-                pneed = need;
-                pinside = inside;
-                po1 = o1;
                 lane_fence<GLOBAL>();
             }
-            if (status == ST_NONE && (__ballot(pneed && po1 < S && (pinside || !(po1 & 1ull))) & gmask))
-                status = ST_CONFLICT;
+            // the last step's claims, also where the attempt overflowed: an attempt that one of
+            // them displaced must learn of it
+            const bool beaten = pneed && settle_claim(a, S, pinside, po1);
+            if (status == ST_NONE && (__ballot(beaten) & gmask)) status = ST_CONFLICT;
             if (status == ST_NONE) status = ST_CAND;
         }
         if (!GLOBAL && status == ST_CAND)
@@ -746,7 +778,7 @@ __global__ __launch_bounds__(256) void k_cavity_b(RoundArgs a) {
     PredStats st;
     uint8_t status = ST_NONE;
     const uint32_t p = a.cand_pt[i];
-    const unsigned long long S = a.round_hi | (2ull * a.cand_rank[i]);
+    const unsigned long long S = claim_stamp(a, i);
     const Vert pv = a.V[p];
     const P3 P = {pv.x, pv.y, pv.z};
     // start as in k_cavity_g, probing 32 records on either side of p
@@ -868,7 +900,9 @@ __global__ __launch_bounds__(256) void k_cavity_b(RoundArgs a) {
                 cn = T[c].n;
             }
             // the previous step's claims (as in k_cavity_g)
-            if (__syncthreads_or(pneed && po1 < S && (pinside || !(po1 & 1ull)))) {
+            const bool beaten = pneed && settle_claim(a, S, pinside, po1);
+            pneed = false;
+            if (__syncthreads_or(beaten)) {
                 status = ST_CONFLICT;
                 break;
             }
@@ -928,6 +962,9 @@ __global__ __launch_bounds__(256) void k_cavity_b(RoundArgs a) {
                 no += s_cnt[1][v];
             }
             __syncthreads();
+            pneed = need;
+            pinside = inside;
+            po1 = o1;
             if (ncav + ni > capL || nbnd + no > capF || s_flag) {
                 status = ST_OVERFLOW;
                 break;
@@ -944,14 +981,11 @@ __global__ __launch_bounds__(256) void k_cavity_b(RoundArgs a) {
             }
             ncav += ni;
             nbnd += no;
-            pneed = need;
-            pinside = inside;
-            po1 = o1;
             if (GLOBAL) __threadfence_block();
             __syncthreads();
         }
-        if (status == ST_NONE && __syncthreads_or(pneed && po1 < S && (pinside || !(po1 & 1ull))))
-            status = ST_CONFLICT;
+        const bool beaten = pneed && settle_claim(a, S, pinside, po1);
+        if (status == ST_NONE && __syncthreads_or(beaten)) status = ST_CONFLICT;
         if (status == ST_NONE) status = ST_CAND;
     }
     if (!GLOBAL && status == ST_CAND)
@@ -975,13 +1009,12 @@ __global__ __launch_bounds__(256) void k_cavity_b(RoundArgs a) {
 }
 
 // Winner test, slot reservation and DelaunayBall (Sec. 2.5), GL lanes per candidate, all in
-// one wave.  An attempt wins iff no lower attempt touched a tetrahedron of its cavity (the
-// claim word still holds its stamp) and the lowest claim on each of its outer tetrahedra is
-// an outer claim (a lower attempt with that tetrahedron in its cavity then loses on it);
-// winners of one round therefore have disjoint cavities, and no cavity meets another
-// winner's outer tetrahedra, so winners build concurrently without further coordination
-// (claim words are only written by the cavity kernel, so the test of one candidate is not
-// affected by the building of another).
+// one wave.  An attempt wins iff it completed its cavity and is not marked as lost (see the
+// head of this file); winners have disjoint cavities and no cavity meets another winner's
+// outer tetrahedra, so they build concurrently without further coordination.  Reading the one
+// mark instead of the claim words of every cavity and outer tetrahedron (about 47 random
+// records) and building in registers took the launches of about 79,000 candidates on 1e7
+// uniform points from 303 to 201 us; the kernel waits on its random 64-byte records.
 //
 // The ball takes the cavity's own slots (and F - C more when it is larger).  The
 // tetrahedron on boundary facet f of cavity tetrahedron k is k with vertex f replaced by p
@@ -990,7 +1023,8 @@ __global__ __launch_bounds__(256) void k_cavity_b(RoundArgs a) {
 // tetrahedron.  Its other three facets pass through p and one edge of its boundary facet;
 // the cavity boundary is a closed surface, so each edge lies on exactly two boundary
 // facets, and the two new tetrahedra on them are the siblings.  They are paired through a
-// hash table of edges in LDS.  Balls too large for the table pair siblings by pivoting
+// hash table of edges in LDS, and each record is stored once it is complete (one row of
+// vertices, one of neighbours).  Balls too large for the table pair siblings by pivoting
 // around the edge through copies of the cavity tetrahedra instead.
 constexpr uint32_t HT = 128;             // edge table entries per candidate
 constexpr uint32_t HT_MAX_FACETS = 64;   // balls up to this size use the table (load <= 3/4)
@@ -1007,6 +1041,19 @@ __device__ __forceinline__ void group_fence() {
 
 __device__ __forceinline__ uint32_t edge_hash(unsigned long long key) {
     return (uint32_t)((key * 0x9E3779B97F4A7C15ull) >> 57);  // 7 bits: HT = 128
+}
+
+// the edge of the boundary facet opposite vertex f that lies in facet q of the new tetrahedron
+// with vertices wv: its two vertices other than q and f, the lower one in the upper half
+__device__ __forceinline__ unsigned long long facet_edge(const uint32_t wv[4], int q, int f) {
+    uint32_t e0 = NONE, e1 = NONE;
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+        if (r != q && r != f) {
+            if (e0 == NONE) e0 = wv[r];
+            else e1 = wv[r];
+        }
+    return e0 < e1 ? ((unsigned long long)e0 << 32) | e1 : ((unsigned long long)e1 << 32) | e0;
 }
 
 template <class K, int GL, int BS>
@@ -1039,19 +1086,13 @@ __global__ __launch_bounds__(BS) void k_ball(RoundArgs a) {
     code *ol = static_cast<code *>(a.outc) + (size_t)i * capF;
     uint4 *sv = a.scr_v + (size_t)i * capC;
     typename K::code4 *sn = static_cast<typename K::code4 *>(a.scr_n) + (size_t)i * capC;
-    bool ok = true;
     if (cand) {
         p = a.cand_pt[i];
-        S = a.round_hi | (2ull * a.cand_rank[i]);
+        S = claim_stamp(a, i);
         nc = a.cnt[i];
         nb = a.cnt[stride + i];
-        // winner test
-        // cavity tetrahedra: no lower claim; outer tetrahedra: the lowest claim is an outer
-        // one (any lower attempt with it in its cavity then loses on that claim)
-        for (uint32_t k = gl; k < nc; k += GL) ok &= T[code_slot(cavl[k])].claim == S;
-        for (uint32_t k = gl; k < nb; k += GL) ok &= (T[code_slot(ol[k])].claim & 1ull) != 0;
     }
-    const bool win = cand && (__ballot(!ok) & gmask) == 0;
+    const bool win = cand && a.lost[i] != a.lost_mark;
     // slot reservation by each winner's first lane, one atomic per block: the F - C extra
     // slots are units of fl_take (units below fl_n are free-list entries of earlier rounds,
     // the rest are fresh pool slots from tet_count on); C - F surplus cavity slots are freed
@@ -1092,35 +1133,137 @@ __global__ __launch_bounds__(BS) void k_ball(RoundArgs a) {
     const uint32_t g_u0 = __shfl(u0, (int)gbase), g_fb = __shfl(fb, (int)gbase);
     const unsigned long long tb1 = a.clk ? (unsigned long long)wall_clock64() : 0ull;
     unsigned long long tb2 = tb1;
-    if (built) {
-        const bool table = nb <= HT_MAX_FACETS;
-        // A: copies of the cavity tetrahedra (vertices; for the pivot also the neighbours and
-        // the local index in the spare word); the edge table is cleared
+    if (built && nb <= HT_MAX_FACETS) {
+        // Balls of up to HT_MAX_FACETS facets: lane gl builds the tetrahedra on boundary facets
+        // gl, gl + GL, ... from registers.  Everything read from the cavity is read before the
+        // first store into it.
+        constexpr int NB = (int)HT_MAX_FACETS / GL;
+        uint32_t slot[NB], at[NB];
+        int fq[NB];
+        code oc[NB];
+        uint4 w[NB];
+#pragma unroll
+        for (int k = 0; k < NB; ++k) {
+            const uint32_t b = gl + (uint32_t)(GL * k);
+            if (b < nb) {
+                const uint32_t bc = bl[b];  // local index of the cavity tetrahedron << 2 | facet
+                oc[k] = ol[b];
+                fq[k] = (int)(bc & 3u);
+                w[k] = T[code_slot(cavl[bc >> 2])].v;
+                if (b < nc) {
+                    slot[k] = code_slot(cavl[b]);
+                } else {
+                    const uint32_t u = g_u0 + (b - nc);
+                    slot[k] = u < fln ? a.fl_cur[u] : tc0 + (u - fln);
+                }
+            }
+        }
+        for (uint32_t h = gl; h < HT; h += GL) {
+            s_key[gi][h] = HT_EMPTY;
+            s_val[gi][h][0] = s_val[gi][h][1] = 0xFFFFu;
+        }
+        group_fence();
+        if (a.clk) tb2 = (unsigned long long)wall_clock64();
+        // edges of the boundary facets into the table; facet q of the new tetrahedron holds p
+        // and the edge of the boundary facet without vertex q
+#pragma unroll
+        for (int k = 0; k < NB; ++k) {
+            const uint32_t b = gl + (uint32_t)(GL * k);
+            at[k] = 0;
+            if (b < nb) {
+                const int f = fq[k];
+                uint32_t wv[4] = {w[k].x, w[k].y, w[k].z, w[k].w};
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (r == f) wv[r] = p;
+                w[k] = make_uint4(wv[0], wv[1], wv[2], wv[3]);
+                s_slot[gi][b] = slot[k];
+                nref(T, code_slot(oc[k]), code_facet(oc[k])) = make_code<K>(slot[k], (uint32_t)f);  // the way back
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    if (q == f) continue;
+                    const unsigned long long key = facet_edge(wv, q, f);
+                    uint32_t h = edge_hash(key);
+                    bool placed = false;
+                    for (uint32_t probe = 0; probe < HT && !placed; ++probe) {
+                        const unsigned long long old = atomicCAS(&s_key[gi][h], HT_EMPTY, key);
+                        if (old == HT_EMPTY || old == key) {
+                            s_val[gi][h][old == HT_EMPTY ? 0 : 1] = (uint16_t)((b << 2) | (uint32_t)q);
+                            at[k] |= h << (8 * q);
+                            placed = true;
+                        } else {
+                            h = (h + 1) & (HT - 1);
+                        }
+                    }
+                    if (!placed) atomicOr(&a.ctr->error, ERR_WALK);
+                }
+            }
+        }
+        lane_fence<false>();
+        // the siblings across the three facets through p; then the record, one aligned row of
+        // vertices and one of neighbours
+#pragma unroll
+        for (int k = 0; k < NB; ++k) {
+            const uint32_t b = gl + (uint32_t)(GL * k);
+            if (b < nb) {
+                const int f = fq[k];
+                typename K::code4 n;
+                unsigned lower = 0;  // facets whose sibling stands on a lower boundary facet
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    code c = oc[k];  // facet opposite p: the outer tetrahedron
+                    if (q != f) {
+                        const uint32_t h = (at[k] >> (8 * q)) & 255u;
+                        const uint32_t mine = (b << 2) | (uint32_t)q;
+                        const uint32_t v0 = s_val[gi][h][0], v1 = s_val[gi][h][1];
+                        uint32_t res = v0 == mine ? v1 : v0;
+                        if ((res >> 2) >= nb) {  // an edge on one facet only: never expected
+                            atomicOr(&a.ctr->error, ERR_WALK);
+                            res = mine;
+                        }
+                        c = make_code<K>(s_slot[gi][res >> 2], res & 3u);
+                        if ((res >> 2) < b) lower |= 1u << q;
+                    }
+                    reinterpret_cast<code *>(&n)[q] = c;
+                }
+                T[slot[k]].v = w[k];
+                T[slot[k]].n = n;
+                const uint32_t wv[4] = {w[k].x, w[k].y, w[k].z, w[k].w};
+                if (a.subd && wv[3] != GHOST)
+                    static_cast<SubD *>(a.subd)[slot[k]] =
+                        subdets(vpos(a.V, wv[0]), vpos(a.V, wv[1]), vpos(a.V, wv[2]), vpos(a.V, wv[3]));
+                // vertex hints: a vertex of the boundary from the facets that are lower than
+                // both their neighbours around it (the lowest one there always is), the new
+                // point from the first
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const unsigned around = 0xFu & ~(1u << r) & ~(1u << f);
+                    if (wv[r] != GHOST && (r == f ? b == 0 : !(lower & around))) a.vtet[wv[r]] = slot[k];
+                }
+            }
+        }
+    } else if (built) {
+        // Larger balls: siblings by pivoting around each edge through copies of the cavity
+        // tetrahedra (vertices, neighbours, and the local index in the spare word)
         for (uint32_t k = gl; k < nc; k += GL) {
             const uint32_t c = code_slot(cavl[k]);
             sv[k] = T[c].v;
-            if (!table) {
-                sn[k] = T[c].n;
-                T[c].spare[0] = k;
-            }
+            sn[k] = T[c].n;
+            T[c].spare[0] = k;
         }
-        if (table)
-            for (uint32_t h = gl; h < HT; h += GL) s_key[gi][h] = HT_EMPTY;
         group_fence();
         if (a.clk) tb2 = (unsigned long long)wall_clock64();
-        if (!table) {
-            // B (pivot only): facets between two cavity tetrahedra -> local codes
-            for (uint32_t task = gl; task < 4 * nc; task += GL) {
-                const uint32_t k = task >> 2;
-                const int f = (int)(task & 3u);
-                const code cd = comp(sn[k], f);
-                const uint32_t nt = code_slot(cd);
-                if (T[nt].claim == S)  // only this winner's cavity tetrahedra hold S
-                    reinterpret_cast<code *>(&sn[k])[f] = make_code<K>((uint32_t)T[nt].spare[0], code_facet(cd));
-            }
-            group_fence();
+        // facets between two cavity tetrahedra -> local codes
+        for (uint32_t task = gl; task < 4 * nc; task += GL) {
+            const uint32_t k = task >> 2;
+            const int f = (int)(task & 3u);
+            const code cd = comp(sn[k], f);
+            const uint32_t nt = code_slot(cd);
+            if (T[nt].claim == S)  // only this winner's cavity tetrahedra hold S
+                reinterpret_cast<code *>(&sn[k])[f] = make_code<K>((uint32_t)T[nt].spare[0], code_facet(cd));
         }
-        // C: one new tetrahedron per boundary facet (k, f): k with v_f replaced by p
+        group_fence();
+        // one new tetrahedron per boundary facet (k, f): k with v_f replaced by p
         for (uint32_t b = gl; b < nb; b += GL) {
             uint32_t slot;
             if (b < nc) {
@@ -1148,111 +1291,51 @@ __global__ __launch_bounds__(BS) void k_ball(RoundArgs a) {
             // the new point (vertex f of each) from the first only
             for (int q = 0; q < 4; ++q)
                 if (wv[q] != GHOST && (q != f || b == 0)) a.vtet[wv[q]] = slot;
-            if (table) {
-                // the three facets through p: facet q holds p and the edge of the boundary
-                // facet without vertex q
-                for (int q = 0; q < 4; ++q) {
-                    if (q == f) continue;
-                    uint32_t e0 = NONE, e1 = NONE;
-                    for (int r = 0; r < 4; ++r)
-                        if (r != q && r != f) {
-                            if (e0 == NONE) e0 = wv[r];
-                            else e1 = wv[r];
-                        }
-                    const unsigned long long key = e0 < e1 ? ((unsigned long long)e0 << 32) | e1
-                                                           : ((unsigned long long)e1 << 32) | e0;
-                    uint32_t h = edge_hash(key);
-                    bool placed = false;
-                    for (uint32_t probe = 0; probe < HT && !placed; ++probe) {
-                        const unsigned long long old = atomicCAS(&s_key[gi][h], HT_EMPTY, key);
-                        if (old == HT_EMPTY || old == key) {
-                            s_val[gi][h][old == HT_EMPTY ? 0 : 1] = (uint16_t)((b << 2) | (uint32_t)q);
-                            placed = true;
-                        }
-                        h = (h + 1) & (HT - 1);
-                    }
-                    if (!placed) atomicOr(&a.ctr->error, ERR_WALK);
-                }
-                s_slot[gi][b] = slot;
-            } else {
-                reinterpret_cast<code *>(&sn[kb])[f] = LOC_BOUNDARY | (code)b;
-            }
+            reinterpret_cast<code *>(&sn[kb])[f] = LOC_BOUNDARY | (code)b;
         }
         group_fence();
-        // D: the three siblings of each new tetrahedron
-        if (table) {
-            for (uint32_t b = gl; b < nb; b += GL) {
-                const code me = ol[b];
-                const uint32_t slot = code_slot(me);
-                const int f = code_facet(me);
-                const uint4 cw = sv[bl[b] >> 2];
-                uint32_t wv[4] = {cw.x, cw.y, cw.z, cw.w};
-                wv[f] = p;
-                for (int q = 0; q < 4; ++q) {
-                    if (q == f) continue;
-                    uint32_t e0 = NONE, e1 = NONE;
-                    for (int r = 0; r < 4; ++r)
-                        if (r != q && r != f) {
-                            if (e0 == NONE) e0 = wv[r];
-                            else e1 = wv[r];
-                        }
-                    const unsigned long long key = e0 < e1 ? ((unsigned long long)e0 << 32) | e1
-                                                           : ((unsigned long long)e1 << 32) | e0;
-                    const uint32_t mine = (b << 2) | (uint32_t)q;
-                    uint32_t h = edge_hash(key), res = NONE;
-                    for (uint32_t probe = 0; probe < HT; ++probe) {
-                        if (s_key[gi][h] == key) {
-                            const uint32_t v0 = s_val[gi][h][0], v1 = s_val[gi][h][1];
-                            res = v0 == mine ? v1 : v0;
-                            break;
-                        }
-                        h = (h + 1) & (HT - 1);
-                    }
-                    if (res == NONE) atomicOr(&a.ctr->error, ERR_WALK);
-                    else nref(T, slot, q) = make_code<K>(s_slot[gi][res >> 2], res & 3u);
+        // the three siblings of each new tetrahedron
+        for (uint32_t task = gl; task < 3 * nb; task += GL) {
+            const uint32_t b = task / 3, qi = task - 3 * b;
+            const code me = ol[b];
+            const uint32_t slot = code_slot(me);
+            const int pf = code_facet(me);
+            const int q = (pf + 1 + (int)qi) & 3;  // the three facets through p
+            const uint32_t kb = bl[b] >> 2;
+            const uint4 cw = sv[kb];
+            const uint32_t c4[4] = {cw.x, cw.y, cw.z, cw.w};
+            uint32_t e[2];
+            int ne = 0;
+            for (int r = 0; r < 4; ++r)
+                if (r != q && r != pf) e[ne++] = c4[r];
+            uint32_t k = kb;
+            int f = pf;
+            code res = 0;
+            bool found = false;
+            for (uint32_t guard = 0; guard <= nc + 1; ++guard) {
+                const uint4 cv = sv[k];
+                const uint32_t v4[4] = {cv.x, cv.y, cv.z, cv.w};
+                int xpos = -1;
+                for (int m = 0; m < 4; ++m)
+                    if (m != f && v4[m] != e[0] && v4[m] != e[1]) xpos = m;
+                if (xpos < 0) break;
+                const code lc = comp(sn[k], xpos);
+                if (lc & LOC_BOUNDARY) {
+                    // boundary facet (k, xpos): its new tetrahedron has p at xpos, and
+                    // the facet through p, e0, e1 is opposite its vertex f
+                    res = make_code<K>(code_slot(ol[(size_t)(lc & ~LOC_BOUNDARY)]), (uint32_t)f);
+                    found = true;
+                    break;
                 }
+                k = code_slot(lc);
+                f = code_facet(lc);
+                if (k >= nc) break;
             }
-        } else {
-            for (uint32_t task = gl; task < 3 * nb; task += GL) {
-                const uint32_t b = task / 3, qi = task - 3 * b;
-                const code me = ol[b];
-                const uint32_t slot = code_slot(me);
-                const int pf = code_facet(me);
-                const int q = (pf + 1 + (int)qi) & 3;  // the three facets through p
-                const uint32_t kb = bl[b] >> 2;
-                const uint4 cw = sv[kb];
-                const uint32_t c4[4] = {cw.x, cw.y, cw.z, cw.w};
-                uint32_t e[2];
-                int ne = 0;
-                for (int r = 0; r < 4; ++r)
-                    if (r != q && r != pf) e[ne++] = c4[r];
-                uint32_t k = kb;
-                int f = pf;
-                code res = 0;
-                bool found = false;
-                for (uint32_t guard = 0; guard <= nc + 1; ++guard) {
-                    const uint4 cv = sv[k];
-                    const uint32_t v4[4] = {cv.x, cv.y, cv.z, cv.w};
-                    int xpos = -1;
-                    for (int m = 0; m < 4; ++m)
-                        if (m != f && v4[m] != e[0] && v4[m] != e[1]) xpos = m;
-                    if (xpos < 0) break;
-                    const code lc = comp(sn[k], xpos);
-                    if (lc & LOC_BOUNDARY) {
-                        // boundary facet (k, xpos): its new tetrahedron has p at xpos, and
-                        // the facet through p, e0, e1 is opposite its vertex f
-                        res = make_code<K>(code_slot(ol[(size_t)(lc & ~LOC_BOUNDARY)]), (uint32_t)f);
-                        found = true;
-                        break;
-                    }
-                    k = code_slot(lc);
-                    f = code_facet(lc);
-                    if (k >= nc) break;
-                }
-                if (!found) atomicOr(&a.ctr->error, ERR_WALK);
-                else nref(T, slot, q) = res;
-            }
+            if (!found) atomicOr(&a.ctr->error, ERR_WALK);
+            else nref(T, slot, q) = res;
         }
+    }
+    if (built) {
         // E: cavity slots beyond the ball's size are freed.  The cloud's known live
         // tetrahedron stays live unless it is one of them (the other cavity slots hold the
         // new tetrahedra): then it moves to the ball's first tetrahedron.  Only this rare

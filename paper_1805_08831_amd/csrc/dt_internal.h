@@ -70,7 +70,7 @@ __host__ __device__ __forceinline__ unsigned long long comp(const Codes4W &q, in
 enum : uint8_t {
     ST_NONE = 0,
     ST_CAND = 1,      // cavity built and claimed, waiting for the check
-    ST_CONFLICT = 2,  // met a claim of a lower-ranked insertion
+    ST_CONFLICT = 2,  // met a claim of an attempt that comes before it
     ST_OVERFLOW = 3,  // cavity larger than this round's per-insertion buffer
     ST_DUP = 4,       // exact duplicate of a vertex already in the mesh
     ST_WON = 5,       // inserted
@@ -138,6 +138,13 @@ struct Cloud {
     double box[4];       // grid origin (x, y, z) and scale 2^m / largest extent
 };
 
+// A claim stamp: round, leading bits of the rank, place in the round's list, kind (0 cavity, 1
+// outer).
+constexpr int CLAIM_PLACE_BITS = 21;
+constexpr int CLAIM_RANK_BITS = 26;
+constexpr int CLAIM_ROUND_BITS = 64 - 1 - CLAIM_PLACE_BITS - CLAIM_RANK_BITS;
+constexpr int CLAIM_ROUND_SHIFT = 64 - CLAIM_ROUND_BITS;
+
 // Arguments of one insertion round.  The pool and the code buffers are typed by the
 // kernels' layout (Narrow or Wide): T is K::Rec[tcap], cav and outc are K::code arrays,
 // scr_n is a K::code4 array.
@@ -172,6 +179,7 @@ struct RoundArgs {
     void *outc;                  // [stride][capF] outer codes, then new tetrahedra
     uint32_t *cnt;               // [2][stride] cavity size, boundary size
     uint8_t *status;             // [stride]
+    uint32_t *lost;              // [stride] lost_mark where a claim of the attempt was displaced
     uint4 *scr_v;                // [stride][capC] vertex copies of the winners' cavity tetrahedra
     void *scr_n;                 // [stride][capC] their neighbour codes (pivoting balls)
     uint32_t *fl_cur;            // free list consumed this round
@@ -181,7 +189,9 @@ struct RoundArgs {
     unsigned long long *stat;    // [NSTAT][STAT_SPREAD][STAT_PAD] work statistics
     uint32_t stride, capC, capF, tcap;
     uint32_t hmg;                // capC > 1024: entries of the cavity set in global memory
-    unsigned long long round_hi;  // (0xFFFFFFFF - round) << 32: newer rounds claim lower
+    unsigned long long round_hi;  // the round's part of its stamps: newer rounds claim lower
+    uint32_t lost_mark;          // the round's value in `lost`
+    uint32_t rank_shift;         // bits of the ranks left out of the stamps
     // if set (trace mode): [stride][8] per attempt.  Filter pass: wall clock (100 MHz) at its
     // start, at the walk's end and at its end, then walk steps | cavity steps << 16 | cavity
     // size << 32 | status << 48.  Ball kernel: clock at its start, after the winner test and
