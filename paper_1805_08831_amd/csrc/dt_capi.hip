@@ -1301,7 +1301,15 @@ int insert_clouds(dt_ctx *c, const double *xyz, uint64_t n, const std::vector<ui
         c->log_base = base;
         c->log_n = n;
     }
+    // the first insertions of a new mesh in one block per cloud.  Not under options that speak of
+    // rounds: a limit or a size of rounds, or every round timed.
+    const bool seed = fresh && c->opt.max_rounds == 0 && c->opt.round_size == 0 && c->opt.timing != 1;
+    if (seed)
+        HIPCHK(launch_seed(c->V.p, c->clouds.p, C, 0, c->lord + lv.start[0], lv.size[0], c->dup.p, c->T, c->wide,
+                           c->tcap, c->vtet.p, c->ctr, c->subd, c->stat, c->logged ? c->log_att.p : nullptr,
+                           (uint32_t)base, c->stream));
     if ((rc = sync_ctr(c))) return rc;
+    if (seed) c->mesh_vertices += c->hctr->won;
     c->st.duplicates += c->hctr->dups;
     auto t1 = std::chrono::steady_clock::now();
     // 8. insertion rounds

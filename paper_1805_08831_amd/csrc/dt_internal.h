@@ -278,6 +278,12 @@ hipError_t launch_labels(const Vert *V, uint64_t base, uint64_t n, const Cloud *
 // codes (true) or Tet records with 32-bit codes (false).
 hipError_t launch_init(const Vert *V, Cloud *clouds, uint32_t nclouds, uint32_t first_slot, const uint8_t *dup,
                        void *T, bool wide, uint32_t *vtet, Ctr *ctr, void *subd, hipStream_t s);
+// the first insertions of each cloud of a fresh call in one block's LDS (dt_seed.hip); lord,
+// nlord: the first level's records.  Counts its insertions in ctr->won.
+hipError_t launch_seed(const Vert *V, Cloud *clouds, uint32_t nclouds, uint32_t first_slot, const uint32_t *lord,
+                       uint32_t nlord, const uint8_t *dup, void *T, bool wide, uint32_t tcap, uint32_t *vtet,
+                       Ctr *ctr, void *subd, unsigned long long *stat, uint32_t *log_att, uint32_t vlo,
+                       hipStream_t s);
 hipError_t launch_fill_list(const FillPlan &plan, const uint32_t *lvl_start, const uint32_t *lvl_size,
                             const uint32_t *lvl_bits, const unsigned long long *rank_base, const uint32_t *lord,
                             const uint8_t *dup, const uint32_t *vtet, uint32_t *cand_pt, uint32_t *cand_rank,
