@@ -31,6 +31,7 @@
 
 #include <algorithm>
 #include <cstdlib>
+#include <type_traits>
 
 #include "dt_internal.h"
 #include "dt_predicates.h"
@@ -362,29 +363,39 @@ __device__ __forceinline__ bool settle_claim(const RoundArgs &a, unsigned long l
 // keep both in LDS at (128, 256) with 4 to 64 lanes per insertion; rounds for large
 // cavities use (1024, 2048) with 64 lanes, and beyond that the same 64-lane search keeps
 // both in global memory (the candidate's cavity buffer and its part of the ball scratch).
-constexpr uint32_t LCAPC = 128;
+constexpr uint32_t LCAPC = 128, LHM = 256;
 constexpr uint32_t BIG_CAPC = 1024, BIG_HM = 2048;
 
+// The set: open addressing in a power-of-two table of hm entries, (t << 1 | kind) per entry,
+// or t alone with the kinds as bits of their own (SPLIT: slots of the wide layout take all 32
+// bits; 8-byte entries instead would halve the set that fits the LDS, and the average
+// insertion touches 47 tetrahedra: at 1e6 points a set of 128 sent 2,800 attempts to the
+// rounds for large cavities, 106 ms a pass instead of 39).
 template <class E>
 __device__ __forceinline__ constexpr E mem_empty() {
     return ~(E)0;
 }
 
-// open addressing in a power-of-two table of hm entries, (t << 1 | kind) per entry
 __device__ __forceinline__ uint32_t mem_hash(uint32_t t, uint32_t hm) {
     return (t * 2654435761u) >> (32 - __builtin_ctz(hm));
 }
 
+// tetrahedron of an entry
+template <bool SPLIT, class E>
+__device__ __forceinline__ uint32_t mem_tet(E e) {
+    return (uint32_t)(SPLIT ? e : e >> 1);
+}
+
 // kind of tetrahedron t in the set (0 cavity, 1 outer) or -1; a set in global memory is
 // read at device scope, past any vector L1 copy, since other lanes fill it by atomics
-template <bool GLOBAL, class E>
-__device__ __forceinline__ int mem_find(E *mem, uint32_t hm, uint32_t t) {
+template <bool GLOBAL, bool SPLIT, class E>
+__device__ __forceinline__ int mem_find(E *mem, const uint32_t *kinds, uint32_t hm, uint32_t t) {
     uint32_t h = mem_hash(t, hm);
     for (uint32_t probe = 0; probe < hm; ++probe) {
         const E e =
             GLOBAL ? __hip_atomic_load(&mem[h], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : mem[h];
         if (e == mem_empty<E>()) return -1;
-        if ((e >> 1) == (E)t) return (int)(e & 1u);
+        if (mem_tet<SPLIT>(e) == t) return SPLIT ? (int)(kinds[h >> 5] >> (h & 31u) & 1u) : (int)(e & 1u);
         h = (h + 1) & (hm - 1);
     }
     return -1;
@@ -392,17 +403,19 @@ __device__ __forceinline__ int mem_find(E *mem, uint32_t hm, uint32_t t) {
 
 // adds t with `kind`: 1 if this call added it (its entry is then mem[*at]), 0 if it was
 // there, -1 if the set is full
-template <class E>
-__device__ __forceinline__ int mem_insert(E *mem, uint32_t hm, uint32_t t, uint32_t kind, uint32_t *at) {
+template <bool SPLIT, class E>
+__device__ __forceinline__ int mem_insert(E *mem, uint32_t *kinds, uint32_t hm, uint32_t t, uint32_t kind,
+                                          uint32_t *at) {
     uint32_t h = mem_hash(t, hm);
-    const E e = ((E)t << 1) | (E)kind;
+    const E e = SPLIT ? (E)t : ((E)t << 1) | (E)kind;
     for (uint32_t probe = 0; probe < hm; ++probe) {
         const E old = atomicCAS(&mem[h], mem_empty<E>(), e);
         if (old == mem_empty<E>()) {
+            if (SPLIT && kind) atomicOr(&kinds[h >> 5], 1u << (h & 31u));
             *at = h;
             return 1;
         }
-        if ((old >> 1) == (E)t) return 0;
+        if (mem_tet<SPLIT>(old) == t) return 0;
         h = (h + 1) & (hm - 1);
     }
     return -1;
@@ -440,13 +453,15 @@ __device__ __forceinline__ void lane_fence() {
 template <class K, int GS, uint32_t CAPL, uint32_t HM, bool GLOBAL, bool FULL, bool DEFER>
 __global__ __launch_bounds__(256) void k_cavity_g(RoundArgs a) {
     using code = typename K::code;
-    using E = typename K::set_t;
+    constexpr bool SPLIT = K::SPLIT && !GLOBAL;
+    using E = std::conditional_t<GLOBAL, typename K::set_t, uint32_t>;
     constexpr uint32_t GPB = 256 / GS;  // insertions per 256-thread block
     constexpr uint32_t NP = GS / 4;     // cavity tetrahedra expanded per step
     // LDS queue entries: (slot of the tetrahedron's entry in the set << 2 | facet it was
     // entered through), 16 bits; the global queue holds (tetrahedron << 2 | facet)
     __shared__ uint16_t s_cav[GPB][GLOBAL ? 1 : CAPL];
     __shared__ E s_mem[GPB][GLOBAL ? 1 : HM];
+    __shared__ uint32_t s_kinds[GPB][SPLIT ? HM / 32 : 1];
     typename K::Rec *const T = static_cast<typename K::Rec *>(a.T);
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t gl = threadIdx.x & (GS - 1);
@@ -577,10 +592,13 @@ __global__ __launch_bounds__(256) void k_cavity_g(RoundArgs a) {
         // the candidate's part of the ball scratch, which the ball kernel uses only later
         const uint32_t hms = GLOBAL ? a.hmg : HM;
         E *mem = GLOBAL ? reinterpret_cast<E *>(a.scr_v + (size_t)i * a.capC) : s_mem[gi];
+        uint32_t *kinds = s_kinds[gi];
         if (status == ST_NONE) {
             // Cavity.  Step k expands cavity tetrahedra k0 .. k0 + NP - 1, lane (slot, facet)
             // = (gl / 4, gl % 4).
             for (uint32_t h = gl; h < hms; h += GS) mem[h] = mem_empty<E>();
+            if (SPLIT)
+                for (uint32_t h = gl; h < hms / 32; h += GS) kinds[h] = 0u;
             lane_fence<GLOBAL>();
             // each step's claims are settled at the next step (or after the last), once that
             // step's loads are in flight, so that the atomics' latency overlaps them; the
@@ -590,7 +608,7 @@ __global__ __launch_bounds__(256) void k_cavity_g(RoundArgs a) {
             if (gl == 0) {
                 po1 = atomicMin(&T[t].claim, S);
                 uint32_t at = 0;
-                mem_insert(mem, hms, t, 0u, &at);
+                mem_insert<SPLIT>(mem, kinds, hms, t, 0u, &at);
                 if (GLOBAL) cavg[0] = make_code<K>(t, 0u);
                 else cavl[0] = (uint16_t)(at << 2);
             }
@@ -608,7 +626,7 @@ __global__ __launch_bounds__(256) void k_cavity_g(RoundArgs a) {
                         cd = cavg[slot];
                     } else {
                         const uint32_t q = cavl[slot];
-                        cd = make_code<K>((uint32_t)(mem[q >> 2] >> 1), q & 3u);
+                        cd = make_code<K>(mem_tet<SPLIT>(mem[q >> 2]), q & 3u);
                     }
                 }
                 const uint32_t c = code_slot(cd);
@@ -629,7 +647,7 @@ __global__ __launch_bounds__(256) void k_cavity_g(RoundArgs a) {
                 }
                 const code ncode = comp(cn, f);
                 const uint32_t u = code_slot(ncode);
-                const int kind = act ? mem_find<GLOBAL>(mem, hms, u) : -1;  // 0: in this cavity, 1: outside it
+                const int kind = act ? mem_find<GLOBAL, SPLIT>(mem, kinds, hms, u) : -1;  // 0: in this cavity, 1: outside it
                 const bool need = act && kind < 0;
                 if (need) uw = T[u].v;
                 bool inside = false, undecided = false;
@@ -689,7 +707,7 @@ __global__ __launch_bounds__(256) void k_cavity_g(RoundArgs a) {
                 // step is queued (if inside) by the lane that records it
                 int ins = 0;
                 uint32_t at = 0;
-                if (need) ins = mem_insert(mem, hms, u, inside ? 0u : 1u, &at);
+                if (need) ins = mem_insert<SPLIT>(mem, kinds, hms, u, inside ? 0u : 1u, &at);
                 const bool first_in = ins == 1 && inside;
                 const bool outside = (act && kind == 1) || (need && !inside);  // boundary facet (c, f)
                 const unsigned long long mi = __ballot(first_in) & gmask;
@@ -726,7 +744,7 @@ __global__ __launch_bounds__(256) void k_cavity_g(RoundArgs a) {
         if (!GLOBAL && status == ST_CAND)
             for (uint32_t k = gl; k < ncav; k += GS) {
                 const uint32_t q = cavl[k];
-                cavg[k] = make_code<K>((uint32_t)(mem[q >> 2] >> 1), q & 3u);
+                cavg[k] = make_code<K>(mem_tet<SPLIT>(mem[q >> 2]), q & 3u);
             }
         if (clocked && gl == 0) {
             unsigned long long *r = a.clk + 8ull * i;
@@ -764,9 +782,11 @@ __global__ __launch_bounds__(256) void k_cavity_g(RoundArgs a) {
 template <class K, uint32_t CAPL, uint32_t HM, bool GLOBAL>
 __global__ __launch_bounds__(256) void k_cavity_b(RoundArgs a) {
     using code = typename K::code;
-    using E = typename K::set_t;
+    constexpr bool SPLIT = K::SPLIT && !GLOBAL;
+    using E = std::conditional_t<GLOBAL, typename K::set_t, uint32_t>;
     __shared__ uint16_t s_cav[GLOBAL ? 1 : CAPL];
     __shared__ E s_mem[GLOBAL ? 1 : HM];
+    __shared__ uint32_t s_kinds[SPLIT ? HM / 32 : 1];
     __shared__ uint32_t s_cnt[2][4];
     __shared__ int s_flag;
     typename K::Rec *const T = static_cast<typename K::Rec *>(a.T);
@@ -860,8 +880,11 @@ __global__ __launch_bounds__(256) void k_cavity_b(RoundArgs a) {
     code *cavg = static_cast<code *>(a.cav) + (size_t)i * a.capC;
     const uint32_t hms = GLOBAL ? a.hmg : HM;
     E *mem = GLOBAL ? reinterpret_cast<E *>(a.scr_v + (size_t)i * a.capC) : s_mem;
+    uint32_t *kinds = s_kinds;
     if (status == ST_NONE) {
         for (uint32_t h = tid; h < hms; h += 256) mem[h] = mem_empty<E>();
+        if (SPLIT)
+            for (uint32_t h = tid; h < hms / 32; h += 256) kinds[h] = 0u;
         if (GLOBAL) __threadfence_block();
         __syncthreads();
         bool pneed = tid == 0, pinside = true;
@@ -869,7 +892,7 @@ __global__ __launch_bounds__(256) void k_cavity_b(RoundArgs a) {
         if (tid == 0) {
             po1 = atomicMin(&T[t].claim, S);
             uint32_t at = 0;
-            mem_insert(mem, hms, t, 0u, &at);
+            mem_insert<SPLIT>(mem, kinds, hms, t, 0u, &at);
             if (GLOBAL) cavg[0] = make_code<K>(t, 0u);
             else s_cav[0] = (uint16_t)(at << 2);
         }
@@ -887,7 +910,7 @@ __global__ __launch_bounds__(256) void k_cavity_b(RoundArgs a) {
                     cd = cavg[slot];
                 } else {
                     const uint32_t qe = s_cav[slot];
-                    cd = make_code<K>((uint32_t)(mem[qe >> 2] >> 1), qe & 3u);
+                    cd = make_code<K>(mem_tet<SPLIT>(mem[qe >> 2]), qe & 3u);
                 }
             }
             const uint32_t c = code_slot(cd);
@@ -908,7 +931,7 @@ __global__ __launch_bounds__(256) void k_cavity_b(RoundArgs a) {
             }
             const code ncode = comp(cn, f);
             const uint32_t u = code_slot(ncode);
-            const int kind = act ? mem_find<GLOBAL>(mem, hms, u) : -1;
+            const int kind = act ? mem_find<GLOBAL, SPLIT>(mem, kinds, hms, u) : -1;
             const bool need = act && kind < 0;
             if (need) uw = T[u].v;
             bool inside = false;
@@ -939,7 +962,7 @@ __global__ __launch_bounds__(256) void k_cavity_b(RoundArgs a) {
             if (need) o1 = atomicMin(&T[u].claim, inside ? S : S + 1);
             int ins = 0;
             uint32_t at = 0;
-            if (need) ins = mem_insert(mem, hms, u, inside ? 0u : 1u, &at);
+            if (need) ins = mem_insert<SPLIT>(mem, kinds, hms, u, inside ? 0u : 1u, &at);
             const bool first_in = ins == 1 && inside;
             const bool outside = (act && kind == 1) || (need && !inside);
             const unsigned long long mi = __ballot(first_in), mo = __ballot(outside);
@@ -991,7 +1014,7 @@ __global__ __launch_bounds__(256) void k_cavity_b(RoundArgs a) {
     if (!GLOBAL && status == ST_CAND)
         for (uint32_t k = tid; k < ncav; k += 256) {
             const uint32_t qe = s_cav[k];
-            cavg[k] = make_code<K>((uint32_t)(mem[qe >> 2] >> 1), qe & 3u);
+            cavg[k] = make_code<K>(mem_tet<SPLIT>(mem[qe >> 2]), qe & 3u);
         }
     if (tid == 0) {
         a.status[i] = status;
@@ -1463,7 +1486,6 @@ constexpr uint32_t DEFER_BLOCKS = 1024;
 template <class K>
 static hipError_t launch_round_k(const RoundArgs &a, uint32_t max_cand, uint32_t lanes, uint32_t large_lanes,
                                  bool exact, hipStream_t s, hipEvent_t *ev) {
-    constexpr uint32_t LHM = K::LHM;
     if (ev) hipEventRecord(ev[0], s);
     // regular rounds: the filter-only kernel over the round's list, then the exact kernel over
     // the attempts it handed on (a short grid-stride pass; nothing to do for most rounds);
@@ -1531,7 +1553,6 @@ namespace {
 
 template <class K>
 void *cavity_filter_kernel(uint32_t lanes) {
-    constexpr uint32_t LHM = K::LHM;
     switch (lanes) {
     case 4: return (void *)k_cavity_g<K, 4, LCAPC, LHM, false, false, false>;
     case 8: return (void *)k_cavity_g<K, 8, LCAPC, LHM, false, false, false>;
@@ -1564,8 +1585,8 @@ hipError_t launch_round_graph(RoundGraph *graphs, const FillPlan &plan, const Fi
     const uint32_t fill_count = plan.off[plan.nblk];
     const uint32_t gl_ball = L == 64 ? 64u : 16u;
     void *k_cav = wide ? cavity_filter_kernel<Wide>(L) : cavity_filter_kernel<Narrow>(L);
-    void *k_exact = wide ? (void *)k_cavity_g<Wide, EXACT_LANES, LCAPC, Wide::LHM, false, true, true>
-                         : (void *)k_cavity_g<Narrow, EXACT_LANES, LCAPC, Narrow::LHM, false, true, true>;
+    void *k_exact = wide ? (void *)k_cavity_g<Wide, EXACT_LANES, LCAPC, LHM, false, true, true>
+                         : (void *)k_cavity_g<Narrow, EXACT_LANES, LCAPC, LHM, false, true, true>;
     void *k_b = wide ? (gl_ball == 64 ? (void *)k_ball<Wide, 64, BALL_BLOCK> : (void *)k_ball<Wide, 16, BALL_BLOCK>)
                      : (gl_ball == 64 ? (void *)k_ball<Narrow, 64, BALL_BLOCK> : (void *)k_ball<Narrow, 16, BALL_BLOCK>);
     // arguments (copied into the graph when set)

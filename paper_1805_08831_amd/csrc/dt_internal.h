@@ -48,15 +48,15 @@ struct Narrow {
     using Rec = Tet;
     using code = uint32_t;
     using code4 = uint4;
-    using set_t = uint32_t;                // cavity-set entry (slot << 1 | kind)
-    static constexpr uint32_t LHM = 256;   // regular cavity set entries in LDS
+    using set_t = uint32_t;                // cavity-set entry in global memory (slot << 1 | kind)
+    static constexpr bool SPLIT = false;
 };
 struct Wide {
     using Rec = TetW;
     using code = unsigned long long;
     using code4 = Codes4W;
     using set_t = unsigned long long;
-    static constexpr uint32_t LHM = 128;   // same LDS bytes as the narrow set
+    static constexpr bool SPLIT = true;    // the kinds of a set in LDS stand apart: a slot takes all 32 bits
 };
 
 __host__ __device__ __forceinline__ uint32_t comp(uint4 q, int k) {
