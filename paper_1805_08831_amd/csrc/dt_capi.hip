@@ -623,7 +623,7 @@ int enqueue_round(dt_ctx *c, int ci, int ni, int oi, uint32_t max_cand, uint32_t
     // graph-launched: regular rounds with the snapshot written by the round-end kernel,
     // neither timed nor clocked (their events and clearing stay outside graphs)
     const bool graph = c->opt.graph_rounds && c->ring_direct && !slice && !timed && !a.clk && max_cand &&
-                       capC <= DEFAULT_CAVITY_CAP;
+                       capC <= DEFAULT_CAVITY_CAP && c->hctr->fl_n <= ROLL_CARRY;
     if (graph) {
         const FillPlan none{};
         const FillArgs nofill{nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
@@ -647,9 +647,9 @@ int enqueue_round(dt_ctx *c, int ci, int ni, int oi, uint32_t max_cand, uint32_t
     c->fl_idx ^= 1;
     if (c->ring_direct) {
         c->slot_tag[slot] = ++c->tag_counter;
-        HIPCHK(launch_round_end(a, max_cand, c->stream, &c->hring[slot], &c->hseq[slot], c->slot_tag[slot]));
+        HIPCHK(launch_round_end(a, c->hctr->fl_n, c->stream, &c->hring[slot], &c->hseq[slot], c->slot_tag[slot]));
     } else {
-        HIPCHK(launch_round_end(a, max_cand, c->stream, nullptr, nullptr, 0));
+        HIPCHK(launch_round_end(a, c->hctr->fl_n, c->stream, nullptr, nullptr, 0));
         HIPCHK(hipMemcpyAsync(&c->hring[slot], c->ctr, sizeof(Ctr), hipMemcpyDeviceToHost, c->stream));
         if (c->evdone[slot]) HIPCHK(hipEventRecord(c->evdone[slot], c->stream));
     }

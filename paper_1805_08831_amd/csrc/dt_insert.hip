@@ -24,8 +24,8 @@
 //              LDS table of boundary edges (pivoting around each boundary edge through copies
 //              of the cavity tetrahedra for large balls).  Freed
 //              slots are reused in later rounds (Sec. 2.5 end, Sec. 3.6).
-// Then k_compact queues losers for the next round with their rank, and overflowing
-// cavities for rounds with larger per-insertion buffers.
+// The ball kernel queues losers for the next round with their rank, and overflowing cavities
+// for rounds with larger per-insertion buffers; k_roll ends the round.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -78,31 +78,40 @@ __device__ __forceinline__ void add_stat(unsigned long long *stat, int id, unsig
         atomicAdd(&stat[((size_t)id * STAT_SPREAD + (blockIdx.x % STAT_SPREAD)) * STAT_PAD], (unsigned long long)s);
 }
 
+// the same for a flag per thread
+__device__ __forceinline__ void add_count(unsigned long long *stat, int id, bool v) {
+    const unsigned long long m = __ballot(v);
+    if ((threadIdx.x & 63) == 0 && m)
+        atomicAdd(&stat[((size_t)id * STAT_SPREAD + (blockIdx.x % STAT_SPREAD)) * STAT_PAD],
+                  (unsigned long long)__popcll(m));
+}
+
 // Reserves v units of the counter *count per thread with one atomic per block (the block is
-// NW waves; every thread must call it): returns the first unit of this thread's range.
-// tmp: NW + 1 words of LDS the block does not use meanwhile.
-template <int NW = 4>
-__device__ __forceinline__ uint32_t block_reserve(uint32_t v, uint32_t *count, uint32_t *tmp) {
-    uint32_t *s_wave = tmp, &s_base = tmp[NW];
+// NW waves; every thread must call it): returns the first unit of this thread's range.  U may
+// hold two counters of 32 bits in one of 64.  tmp: NW + 1 words of LDS the block does not use
+// meanwhile.
+template <int NW, class U>
+__device__ __forceinline__ U block_reserve(U v, U *count, U *tmp) {
+    U *s_wave = tmp, &s_base = tmp[NW];
     const uint32_t lane = threadIdx.x & 63u, wid = threadIdx.x >> 6;
-    uint32_t x = v;
+    U x = v;
     for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t y = __shfl_up(x, o, 64);
+        const U y = __shfl_up(x, o, 64);
         if (lane >= (uint32_t)o) x += y;
     }
     if (lane == 63) s_wave[wid] = x;
     __syncthreads();
     if (threadIdx.x == 0) {
-        uint32_t t = 0;
+        U t = 0;
         for (int w = 0; w < NW; ++w) {
-            const uint32_t c = s_wave[w];
+            const U c = s_wave[w];
             s_wave[w] = t;
             t += c;
         }
-        s_base = t ? atomicAdd(count, t) : 0u;
+        s_base = t ? atomicAdd(count, t) : U(0);
     }
     __syncthreads();
-    const uint32_t r = s_base + s_wave[wid] + x - v;
+    const U r = s_base + s_wave[wid] + x - v;
     __syncthreads();  // tmp may be reused after the call
     return r;
 }
@@ -264,7 +273,7 @@ __global__ __launch_bounds__(FILL_BLOCK) void k_fill(FillPlan plan, const uint32
         }
     }
     __shared__ uint32_t s_tmp[FILL_BLOCK / 64 + 1];
-    const uint32_t pos = block_reserve<FILL_BLOCK / 64>(ok ? 1u : 0u, ncand, s_tmp);
+    const uint32_t pos = block_reserve<FILL_BLOCK / 64, uint32_t>(ok ? 1u : 0u, ncand, s_tmp);
     if (ok) {
         cand_pt[pos] = p;
         cand_rank[pos] = r;
@@ -1101,7 +1110,8 @@ __global__ __launch_bounds__(BS) void k_ball(RoundArgs a) {
     const uint32_t stride = a.stride, capC = a.capC, capF = a.capF;
     unsigned cav_w = 0, bnd_w = 0;
     const unsigned long long tb0 = a.clk ? (unsigned long long)wall_clock64() : 0ull;
-    const bool cand = i < ncand && a.status[i] == ST_CAND;
+    const uint8_t status = i < ncand ? a.status[i] : (uint8_t)ST_NONE;
+    const bool cand = status == ST_CAND;
     uint32_t p = 0, nc = 0, nb = 0;
     unsigned long long S = 0;
     const code *cavl = static_cast<const code *>(a.cav) + (size_t)i * capC;
@@ -1116,12 +1126,22 @@ __global__ __launch_bounds__(BS) void k_ball(RoundArgs a) {
         nb = a.cnt[stride + i];
     }
     const bool win = cand && a.lost[i] != a.lost_mark;
-    // slot reservation by each winner's first lane, one atomic per block: the F - C extra
-    // slots are units of fl_take (units below fl_n are free-list entries of earlier rounds,
-    // the rest are fresh pool slots from tet_count on); C - F surplus cavity slots are freed
-    const bool leader = win && gl == 0;
+    // What each attempt takes, by its first lane, with one atomic per block on one counter:
+    // slots for a winner (units below fl_n are free-list entries of earlier rounds, the rest
+    // fresh pool slots from tet_count on; C - F surplus cavity slots are freed), a place in the
+    // next list for an attempt that tries again (ST_FULL: a round whose exact pass was not
+    // launched left it).  In rounds over overflowed attempts both lists are one.
+    const bool first = gl == 0, leader = win && first;
     const uint32_t need = leader && nb > nc ? nb - nc : 0u;
-    const uint32_t u0 = block_reserve<BS / 64>(need, &a.ctr->fl_take, &s_slot[0][0]);
+    const bool ovf = first && status == ST_OVERFLOW, one_list = a.nnext_ptr == a.novf_ptr;
+    const bool again = first && (status == ST_CONFLICT || status == ST_WALK || status == ST_FULL || (cand && !win));
+    const bool listed = again || (ovf && one_list);
+    const uint32_t list0 = *a.nnext_ptr;  // advanced at the round's end
+    const unsigned long long took =
+        block_reserve<BS / 64, unsigned long long>(need | ((unsigned long long)listed << 32),
+                                                   reinterpret_cast<unsigned long long *>(&a.ctr->fl_take),
+                                                   &s_key[0][0]);
+    const uint32_t u0 = (uint32_t)took;
     const uint32_t fln = a.ctr->fl_n, tc0 = a.ctr->tet_count;
     const bool full = need && u0 + need > fln && (uint64_t)tc0 + (u0 + need - fln) > a.tcap;
     if (full) {
@@ -1148,10 +1168,12 @@ __global__ __launch_bounds__(BS) void k_ball(RoundArgs a) {
             if (slot != NONE) ++q;
         }
         atomicOr(&a.ctr->error, ERR_POOL);
+        const uint32_t at = list0 + atomicAdd(&a.ctr->next_n, 1u);
+        a.next_pt[at] = p;
+        a.next_rank[at] = a.cand_rank[i];
     }
     const bool lbuilt = leader && !full;
     const uint32_t fb = lbuilt && nc > nb ? atomicAdd(&a.ctr->fl_next, nc - nb) : 0u;  // rare
-    if (cand && gl == 0) a.status[i] = lbuilt ? ST_WON : ST_CONFLICT;
     const bool built = __shfl((int)lbuilt, (int)gbase) != 0;
     const uint32_t g_u0 = __shfl(u0, (int)gbase), g_fb = __shfl(fb, (int)gbase);
     const unsigned long long tb1 = a.clk ? (unsigned long long)wall_clock64() : 0ull;
@@ -1386,84 +1408,98 @@ __global__ __launch_bounds__(BS) void k_ball(RoundArgs a) {
         r[2] = built ? tb2 : 0ull;
         r[3] = built ? (unsigned long long)wall_clock64() : 0ull;
     }
+    // the lists, behind the building: no winner waits for these loads
+    if (listed) {
+        const uint32_t at = list0 + (uint32_t)(took >> 32);
+        a.next_pt[at] = a.cand_pt[i];
+        a.next_rank[at] = a.cand_rank[i];
+    }
+    if (ovf && !one_list) {
+        const uint32_t at = atomicAdd(a.novf_ptr, 1u);
+        a.ovf_pt[at] = a.cand_pt[i];
+        a.ovf_rank[at] = a.cand_rank[i];
+    }
+    if (first && i < ncand && (status == ST_NONE || status == ST_ERROR)) atomicOr(&a.ctr->error, ERR_WALK);
+    if (a.log_att && first && i < ncand) atomicAdd(&a.log_att[a.cand_pt[i] - a.vlo], 1u);
     add_stat(a.stat, STAT_CAV_TETS, cav_w);
     add_stat(a.stat, STAT_BND_FACETS, bnd_w);
+    add_count(a.stat, STAT_WON, lbuilt);
+    add_count(a.stat, STAT_OVERFLOWS, ovf);
+    add_count(a.stat, STAT_WALK_CAPS, first && status == ST_WALK);
 }
 
 // ------------------------------------------------------------------ round end
 
-__global__ __launch_bounds__(FILL_BLOCK) void k_compact(RoundArgs a) {
-    constexpr int NW = FILL_BLOCK / 64;
-    __shared__ uint32_t s_tmp[NW + 1];
-    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    const uint32_t ncand = *a.ncand_ptr;
-    const uint8_t s = i < ncand ? a.status[i] : (uint8_t)ST_NONE;
-    // ST_FULL left by a round whose exact pass was not launched: the attempt retries
-    const bool again = i < ncand && (s == ST_CONFLICT || s == ST_CAND || s == ST_WALK || s == ST_FULL);
-    const bool ovf = i < ncand && s == ST_OVERFLOW;
-    if (a.log_att && i < ncand) atomicAdd(&a.log_att[a.cand_pt[i] - a.vlo], 1u);
-    const uint32_t pn = block_reserve<NW>(again ? 1u : 0u, a.nnext_ptr, s_tmp);
-    const uint32_t po = block_reserve<NW>(ovf ? 1u : 0u, a.novf_ptr, s_tmp);
-    if (again) {
-        a.next_pt[pn] = a.cand_pt[i];
-        a.next_rank[pn] = a.cand_rank[i];
-    }
-    if (ovf) {
-        a.ovf_pt[po] = a.cand_pt[i];
-        a.ovf_rank[po] = a.cand_rank[i];
-    }
-    // the round's counts: one atomic per block and counter
-    block_reserve<NW>(again ? 1u : 0u, &a.ctr->conflicts, s_tmp);
-    block_reserve<NW>(ovf ? 1u : 0u, &a.ctr->overflows, s_tmp);
-    block_reserve<NW>(i < ncand && s == ST_WON ? 1u : 0u, &a.ctr->won, s_tmp);
-    block_reserve<NW>(i < ncand && s == ST_DUP ? 1u : 0u, &a.ctr->dups, s_tmp);
-    block_reserve<NW>(i < ncand && s == ST_WALK ? 1u : 0u, &a.ctr->walk_caps, s_tmp);
-    const bool bad = i < ncand && !(again || ovf || s == ST_WON || s == ST_DUP);
-    if (bad) atomicOr(&a.ctr->error, ERR_WALK);
-}
-
-// carry the unused part of this round's free list behind the slots freed this round (as far
-// as the list holds them; k_roll counts the rest)
-__global__ void k_freelist_carry(RoundArgs a) {
+// the unused part of this round's free list goes behind the slots freed this round (as far as
+// the list holds them)
+__device__ __forceinline__ void carry_free(const RoundArgs &a, uint32_t from, uint32_t step) {
     const uint32_t fln = a.ctr->fl_n, take = a.ctr->fl_take, nxt = min(a.ctr->fl_next, a.flcap);
     if (take >= fln) return;
     const uint32_t left = min(fln - take, a.flcap - nxt);
-    for (uint32_t k = blockIdx.x * blockDim.x + threadIdx.x; k < left; k += gridDim.x * blockDim.x)
-        a.fl_next[nxt + k] = a.fl_cur[take + k];
+    for (uint32_t k = from; k < left; k += step) a.fl_next[nxt + k] = a.fl_cur[take + k];
 }
 
-// Round end: statistics summed, the pool's counters advanced.  With `snap` (pinned host
-// memory), the counters are then written there and `seq` (host memory too) is set to `tag`
-// after them with a release at system scope: the host waits for that value instead of for a
-// copy and an event.
-__global__ void k_roll(Ctr *ctr, uint32_t *consumed, uint32_t tcap, uint32_t flcap, const unsigned long long *stat,
-                       Ctr *snap, unsigned long long *seq, unsigned long long tag) {
+__global__ void k_freelist_carry(RoundArgs a) {
+    carry_free(a, blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x);
+}
+
+// Round end, one block: the free list's rest carried, the statistics summed (one wavefront per
+// statistic), the pool's counters advanced.  The ball kernel has queued the attempts that try
+// again; a round thus ends with one launch of about 5 us (a compaction, a carry and a roll
+// kernel took 16).  With `snap` (pinned host memory), the counters are then written there and
+// `seq` (host memory too) is set to `tag` after them with a release at system scope: the host
+// waits for that value instead of for a copy and an event.
+constexpr int ROLL_BLOCK = 1024;
+static_assert(NSTAT * 64 <= ROLL_BLOCK && STAT_SPREAD == 64, "one wavefront sums one statistic");
+
+__global__ __launch_bounds__(ROLL_BLOCK) void k_roll(RoundArgs a, uint32_t *consumed, uint32_t carry, Ctr *snap,
+                                                     unsigned long long *seq, unsigned long long tag) {
+    __shared__ uint32_t s_ovf;  // attempts that overflowed in this round
     const uint32_t t = threadIdx.x;
-    if (t < NSTAT) {
-        unsigned long long sum = 0;
-        for (int k = 0; k < STAT_SPREAD; ++k) sum += stat[((size_t)t * STAT_SPREAD + k) * STAT_PAD];
-        unsigned long long *dst[NSTAT] = {&ctr->attempts, &ctr->walk_steps, &ctr->orient, &ctr->orient_exact,
-                                         &ctr->insphere, &ctr->insphere_exact, &ctr->perturbed,
-                                         &ctr->cav_tets, &ctr->bnd_facets};
-        *dst[t] = sum;
+    Ctr *const ctr = a.ctr;
+    if (t < NSTAT * 64) {
+        unsigned long long x = a.stat[((size_t)(t >> 6) * STAT_SPREAD + (t & 63u)) * STAT_PAD];
+        for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
+        if ((t & 63u) == 0) {
+            const int id = (int)(t >> 6);
+            if (id == STAT_WON) {
+                ctr->won = (uint32_t)x;
+            } else if (id == STAT_WALK_CAPS) {
+                ctr->walk_caps = (uint32_t)x;
+            } else if (id == STAT_OVERFLOWS) {
+                s_ovf = (uint32_t)x - ctr->overflows;
+                ctr->overflows = (uint32_t)x;
+            } else {
+                unsigned long long *dst[STAT_WON] = {&ctr->attempts, &ctr->walk_steps, &ctr->orient, &ctr->orient_exact,
+                                                     &ctr->insphere, &ctr->insphere_exact, &ctr->perturbed,
+                                                     &ctr->cav_tets, &ctr->bnd_facets};
+                *dst[id] = x;
+            }
+        }
     }
+    if (carry) carry_free(a, t, ROLL_BLOCK);
     __syncthreads();
     if (t == 0) {
-    const uint32_t fln = ctr->fl_n, take = ctr->fl_take;
-    if (take > fln) {
-        // units beyond the free list were fresh pool slots (beyond the pool: never used)
-        const unsigned long long tc = (unsigned long long)ctr->tet_count + (take - fln);
-        ctr->tet_count = tc > tcap ? tcap : (uint32_t)tc;
-    }
-    const uint32_t left = take < fln ? fln - take : 0u;
-    const uint32_t nxt = min(ctr->fl_next, flcap), keep = min(left, flcap - nxt);
-    ctr->dropped += (ctr->fl_next - nxt) + (left - keep);
-    ctr->deferred += ctr->ndefer;
-    ctr->ndefer = 0;
-    ctr->fl_n = nxt + keep;
-    ctr->fl_take = 0;
-    ctr->fl_next = 0;
-    *consumed = 0;  // the list this round read from is empty now
+        const uint32_t fln = ctr->fl_n, take = ctr->fl_take;
+        if (take > fln) {
+            // units beyond the free list were fresh pool slots (beyond the pool: never used)
+            const unsigned long long tc = (unsigned long long)ctr->tet_count + (take - fln);
+            ctr->tet_count = tc > a.tcap ? a.tcap : (uint32_t)tc;
+        }
+        const uint32_t left = take < fln ? fln - take : 0u;
+        const uint32_t nxt = min(ctr->fl_next, a.flcap), keep = min(left, a.flcap - nxt);
+        ctr->dropped += (ctr->fl_next - nxt) + (left - keep);
+        ctr->deferred += ctr->ndefer;
+        ctr->ndefer = 0;
+        ctr->fl_n = nxt + keep;
+        ctr->fl_take = 0;
+        ctr->fl_next = 0;
+        // those that try again lost to a conflict, or (rounds over overflowed attempts, whose
+        // two lists are one) overflowed again
+        ctr->conflicts += ctr->next_n - (a.nnext_ptr == a.novf_ptr ? s_ovf : 0u);
+        *a.nnext_ptr += ctr->next_n;
+        ctr->next_n = 0;
+        *consumed = 0;  // the list this round read from is empty now
     }
     if (!snap) return;
     __threadfence_block();
@@ -1471,7 +1507,7 @@ __global__ void k_roll(Ctr *ctr, uint32_t *consumed, uint32_t tcap, uint32_t flc
     static_assert(sizeof(Ctr) % sizeof(uint32_t) == 0, "the snapshot is copied in words");
     const uint32_t *src = reinterpret_cast<const uint32_t *>(ctr);
     uint32_t *dst = reinterpret_cast<uint32_t *>(snap);
-    for (uint32_t k = t; k < sizeof(Ctr) / sizeof(uint32_t); k += blockDim.x) dst[k] = src[k];
+    for (uint32_t k = t; k < sizeof(Ctr) / sizeof(uint32_t); k += ROLL_BLOCK) dst[k] = src[k];
     __threadfence_system();
     __syncthreads();
     if (t == 0) __hip_atomic_store(seq, tag, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
@@ -1539,11 +1575,11 @@ hipError_t launch_round(const RoundArgs &a, bool wide, uint32_t max_cand, uint32
                 : launch_round_k<Narrow>(a, max_cand, lanes, large_lanes, exact, s, ev);
 }
 
-hipError_t launch_round_end(const RoundArgs &a, uint32_t max_cand, hipStream_t s, Ctr *snap,
+hipError_t launch_round_end(const RoundArgs &a, uint32_t free_slots, hipStream_t s, Ctr *snap,
                             unsigned long long *seq, unsigned long long tag) {
-    if (max_cand) k_compact<<<(max_cand + FILL_BLOCK - 1) / FILL_BLOCK, FILL_BLOCK, 0, s>>>(a);
-    k_freelist_carry<<<256, 256, 0, s>>>(a);
-    k_roll<<<1, 64, 0, s>>>(a.ctr, const_cast<uint32_t *>(a.ncand_ptr), a.tcap, a.flcap, a.stat, snap, seq, tag);
+    const bool apart = free_slots > ROLL_CARRY;
+    if (apart) k_freelist_carry<<<256, 256, 0, s>>>(a);
+    k_roll<<<1, ROLL_BLOCK, 0, s>>>(a, const_cast<uint32_t *>(a.ncand_ptr), apart ? 0u : 1u, snap, seq, tag);
     return hipGetLastError();
 }
 
@@ -1593,15 +1629,13 @@ hipError_t launch_round_graph(RoundGraph *graphs, const FillPlan &plan, const Fi
     FillPlan pl = plan;
     FillArgs f = fa;
     RoundArgs ra = a;
-    Ctr *ctr = a.ctr;
     uint32_t *consumed = const_cast<uint32_t *>(a.ncand_ptr);
-    uint32_t tcap = a.tcap, flcap = a.flcap;
-    const unsigned long long *stat = a.stat;
+    uint32_t carry = 1;
     void *fill_args[] = {&pl, &f.lvl_start, &f.lvl_size, &f.lvl_bits, &f.rank_base, &f.lord, &f.dup, &f.vtet,
                          &f.cand_pt, &f.cand_rank, &f.ncand};
     void *round_args[] = {&ra};
-    void *roll_args[] = {&ctr, &consumed, &tcap, &flcap, &stat, &snap, &seq, &tag};
-    hipKernelNodeParams p[7] = {};
+    void *roll_args[] = {&ra, &consumed, &carry, &snap, &seq, &tag};
+    hipKernelNodeParams p[ROUND_GRAPH_NODES] = {};
     auto set = [&](int k, void *fn, uint32_t grid, uint32_t block, void **args) {
         p[k].func = fn;
         p[k].gridDim = dim3(grid ? grid : 1u);
@@ -1615,13 +1649,11 @@ hipError_t launch_round_graph(RoundGraph *graphs, const FillPlan &plan, const Fi
     set(1, k_cav, (max_cand + gpb - 1) / gpb, 256, round_args);
     set(2, k_exact, std::min<uint32_t>((max_cand + 256 / EXACT_LANES - 1) / (256 / EXACT_LANES), DEFER_BLOCKS), 256, round_args);
     set(3, k_b, (max_cand + BALL_BLOCK / gl_ball - 1) / (BALL_BLOCK / gl_ball), BALL_BLOCK, round_args);
-    set(4, (void *)k_compact, (max_cand + FILL_BLOCK - 1) / FILL_BLOCK, FILL_BLOCK, round_args);
-    set(5, (void *)k_freelist_carry, 256, 256, round_args);
-    set(6, (void *)k_roll, 1, 64, roll_args);
+    set(4, (void *)k_roll, 1, ROLL_BLOCK, roll_args);
     hipError_t e;
     if (!g.exec) {
         if ((e = hipGraphCreate(&g.graph, 0)) != hipSuccess) return e;
-        for (int k = 0; k < 7; ++k) {
+        for (int k = 0; k < ROUND_GRAPH_NODES; ++k) {
             e = hipGraphAddKernelNode(&g.node[k], g.graph, k ? &g.node[k - 1] : nullptr, k ? 1 : 0, &p[k]);
             if (e != hipSuccess) return e;
         }
@@ -1630,7 +1662,7 @@ hipError_t launch_round_graph(RoundGraph *graphs, const FillPlan &plan, const Fi
             return e;
         }
     } else {
-        for (int k = 0; k < 7; ++k)
+        for (int k = 0; k < ROUND_GRAPH_NODES; ++k)
             if ((e = hipGraphExecKernelNodeSetParams(g.exec, g.node[k], &p[k])) != hipSuccess) return e;
     }
     return hipGraphLaunch(g.exec, s);

@@ -73,7 +73,6 @@ enum : uint8_t {
     ST_CONFLICT = 2,  // met a claim of an attempt that comes before it
     ST_OVERFLOW = 3,  // cavity larger than this round's per-insertion buffer
     ST_DUP = 4,       // exact duplicate of a vertex already in the mesh
-    ST_WON = 5,       // inserted
     ST_ERROR = 6,     // walk did not terminate (never expected)
     ST_FULL = 7,      // a sign the fp64 filter could not decide: run again with exact predicates
     ST_WALK = 8       // walk stopped at the round's cap: retried next round from where it stopped
@@ -92,7 +91,7 @@ enum : uint32_t {
 // waves do not serialize on one address; k_roll sums them into Ctr.
 enum : int {
     STAT_ATTEMPTS = 0, STAT_WALK, STAT_ORIENT, STAT_ORIENT_EXACT, STAT_INSPHERE, STAT_INSPHERE_EXACT,
-    STAT_PERTURBED, STAT_CAV_TETS, STAT_BND_FACETS, NSTAT
+    STAT_PERTURBED, STAT_CAV_TETS, STAT_BND_FACETS, STAT_WON, STAT_OVERFLOWS, STAT_WALK_CAPS, NSTAT
 };
 constexpr int STAT_SPREAD = 64;
 constexpr int STAT_PAD = 16;  // u64 words per counter (128 bytes)
@@ -102,14 +101,16 @@ constexpr size_t STAT_WORDS = (size_t)NSTAT * STAT_SPREAD * STAT_PAD;
 struct Ctr {
     uint32_t list_count[4];  // lengths of the candidate lists (two normal, two overflow)
     uint32_t fl_n;       // free slots available this round
-    uint32_t fl_take;    // slot units taken this round: unit u < fl_n is free-list entry u,
-                         // unit u >= fl_n is pool slot tet_count + (u - fl_n)
     uint32_t fl_next;    // slots freed this round
+    // one 64-bit counter for the ball kernel's blocks:
+    alignas(8) uint32_t fl_take;  // slot units taken this round: unit u < fl_n is free-list entry u,
+                         // unit u >= fl_n is pool slot tet_count + (u - fl_n)
+    uint32_t next_n;     // candidates this round adds to the next list
     uint32_t tet_count;  // bump pointer of the tetrahedron pool
     uint32_t won;        // insertions so far (this and the other counters below: since the
     uint32_t conflicts;  // last clear), conflicts,
     uint32_t overflows;  // cavity buffer overflows,
-    uint32_t dups;       // duplicates found
+    uint32_t dups;       // duplicates found within the call
     uint32_t error;      // ERR_* flags
     uint32_t init[4];    // sorted positions of the initial tetrahedron's vertices
     uint32_t bad_cloud;  // first cloud found degenerate by the initial-tetrahedron search
@@ -292,10 +293,14 @@ hipError_t launch_fill_list(const FillPlan &plan, const uint32_t *lvl_start, con
 // it, attempts the filter hands on retry in the next round)
 hipError_t launch_round(const RoundArgs &a, bool wide, uint32_t max_cand, uint32_t lanes, uint32_t large_lanes,
                         bool exact, hipStream_t s, hipEvent_t *ev);
-hipError_t launch_round_end(const RoundArgs &a, uint32_t max_cand, hipStream_t s, Ctr *snap,
+// Free-list entries the round-end kernel's one block carries; a longer rest is carried by a
+// kernel of its own, which is launched while the host sees more of them.
+constexpr uint32_t ROLL_CARRY = 1u << 16;
+// free_slots: the free list's length as far as the host knows it (it only chooses the launches)
+hipError_t launch_round_end(const RoundArgs &a, uint32_t free_slots, hipStream_t s, Ctr *snap,
                             unsigned long long *seq, unsigned long long tag);
 // A regular round (cavity buffers of the regular size) as one HIP graph: the fill, the two
-// cavity passes, the DelaunayBall kernel and the three round-end kernels as a chain of kernel
+// cavity passes, the DelaunayBall kernel and the round-end kernel as a chain of kernel
 // nodes.  The graph is built and instantiated once per launch shape (pool layout, lanes per
 // insertion); each later round of that shape only updates the nodes' arguments and grids.
 struct FillArgs {
@@ -306,10 +311,11 @@ struct FillArgs {
     const uint32_t *vtet;
     uint32_t *cand_pt, *cand_rank, *ncand;
 };
+constexpr int ROUND_GRAPH_NODES = 5;
 struct RoundGraph {
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
-    hipGraphNode_t node[7] = {};
+    hipGraphNode_t node[ROUND_GRAPH_NODES] = {};
 };
 constexpr int ROUND_GRAPH_SHAPES = 10;  // pool layout (2) x lanes per insertion (4, 8, 16, 32, 64)
 hipError_t launch_round_graph(RoundGraph *graphs, const FillPlan &plan, const FillArgs &fa, const RoundArgs &a,

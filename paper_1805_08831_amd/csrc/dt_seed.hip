@@ -570,6 +570,7 @@ __global__ __launch_bounds__(SEED_THREADS) void k_seed(const Vert *__restrict__ 
     if (tid == 0) {
         cl->any_live = place(s.hint[0]);
         atomicAdd(&ctr->won, s.won);
+        add(STAT_WON, s.won);
         atomicAdd(&ctr->conflicts, s.lost);
         add(STAT_ATTEMPTS, s.att);
         add(STAT_WALK, s.walk);
