@@ -139,6 +139,7 @@ struct dt_ctx {
         double ms = 0;
     } tuned[64];
     uint32_t *defer = nullptr;             // candidates handed to the exact-predicate pass
+    uint2 *wins = nullptr;                 // winners of a round
     uint32_t *lost = nullptr;              // attempts one of whose claims was displaced
     void *cav = nullptr, *outc = nullptr;  // adjacency codes (4 or 8 bytes each)
     uint32_t *bnd = nullptr, *cnt = nullptr;
@@ -387,7 +388,9 @@ int ensure_round_buffers(dt_ctx *c, uint32_t rmax) {
     }
     dev_free(c, c->cav); dev_free(c, c->bnd); dev_free(c, c->outc); dev_free(c, c->cnt); dev_free(c, c->status);
     dev_free(c, c->scr_v); dev_free(c, c->scr_n); dev_free(c, c->defer); dev_free(c, c->lost);
+    dev_free(c, c->wins);
     c->defer = c->lost = nullptr;
+    c->wins = nullptr;
     c->scr_v = nullptr;
     c->scr_n = nullptr;
     c->cav = c->outc = nullptr;
@@ -409,6 +412,7 @@ int ensure_round_buffers(dt_ctx *c, uint32_t rmax) {
          dev_alloc(c, (void **)&c->status, rmax) == hipSuccess &&
          dev_alloc(c, (void **)&c->defer, rmax * sizeof(uint32_t)) == hipSuccess &&
          dev_alloc(c, (void **)&c->lost, rmax * sizeof(uint32_t)) == hipSuccess &&
+         dev_alloc(c, (void **)&c->wins, rmax * sizeof(uint2)) == hipSuccess &&
          dev_alloc(c, (void **)&c->scr_v, c->bufC * sizeof(uint4)) == hipSuccess &&
          dev_alloc(c, &c->scr_n, c->bufC * 4 * cb) == hipSuccess;
     c->buf_wide = c->wide;
@@ -572,6 +576,7 @@ int enqueue_round(dt_ctx *c, int ci, int ni, int oi, uint32_t max_cand, uint32_t
     a.cnt = c->cnt;
     a.status = c->status;
     a.lost = c->lost;
+    a.wins = c->wins;
     a.fl_cur = c->fl[c->fl_idx];
     a.fl_next = c->fl[c->fl_idx ^ 1];
     a.flcap = c->flcap;
@@ -624,14 +629,20 @@ int enqueue_round(dt_ctx *c, int ci, int ni, int oi, uint32_t max_cand, uint32_t
     // neither timed nor clocked (their events and clearing stay outside graphs)
     const bool graph = c->opt.graph_rounds && c->ring_direct && !slice && !timed && !a.clk && max_cand &&
                        capC <= DEFAULT_CAVITY_CAP && c->hctr->fl_n <= ROLL_CARRY;
+    RoundEnd end{nullptr, nullptr, 0, c->hctr->fl_n};
+    if (c->ring_direct) {
+        c->slot_tag[slot] = ++c->tag_counter;
+        end.snap = &c->hring[slot];
+        end.seq = &c->hseq[slot];
+        end.tag = c->slot_tag[slot];
+    }
     if (graph) {
         const FillPlan none{};
         const FillArgs nofill{nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
                               nullptr, nullptr, &d->list_count[ci]};
         c->fl_idx ^= 1;
-        c->slot_tag[slot] = ++c->tag_counter;
-        HIPCHK(launch_round_graph(c->graphs, plan ? *plan : none, fa ? *fa : nofill, a, c->wide, max_cand, lanes,
-                                  &c->hring[slot], &c->hseq[slot], c->slot_tag[slot], c->stream));
+        HIPCHK(launch_round_graph(c->graphs, plan ? *plan : none, fa ? *fa : nofill, a, c->wide, max_cand, lanes, end,
+                                  c->stream));
         c->slot_cand[slot] = max_cand;
         c->slot_capC[slot] = capC;
         c->st.rounds++;
@@ -642,14 +653,10 @@ int enqueue_round(dt_ctx *c, int ci, int ni, int oi, uint32_t max_cand, uint32_t
     if (plan)
         HIPCHK(launch_fill_list(*plan, fa->lvl_start, fa->lvl_size, fa->lvl_bits, fa->rank_base, fa->lord, fa->dup,
                                 fa->vtet, fa->cand_pt, fa->cand_rank, fa->ncand, c->stream));
-    HIPCHK(launch_round(a, c->wide, max_cand, lanes, c->large_lanes, c->exact_needed, c->stream,
+    HIPCHK(launch_round(a, c->wide, max_cand, lanes, c->large_lanes, c->exact_needed, end, c->stream,
                         timed ? evs : nullptr));
     c->fl_idx ^= 1;
-    if (c->ring_direct) {
-        c->slot_tag[slot] = ++c->tag_counter;
-        HIPCHK(launch_round_end(a, c->hctr->fl_n, c->stream, &c->hring[slot], &c->hseq[slot], c->slot_tag[slot]));
-    } else {
-        HIPCHK(launch_round_end(a, c->hctr->fl_n, c->stream, nullptr, nullptr, 0));
+    if (!c->ring_direct) {
         HIPCHK(hipMemcpyAsync(&c->hring[slot], c->ctr, sizeof(Ctr), hipMemcpyDeviceToHost, c->stream));
         if (c->evdone[slot]) HIPCHK(hipEventRecord(c->evdone[slot], c->stream));
     }
@@ -780,6 +787,7 @@ int complete_round(dt_ctx *c, int slot) {
                 c->hctr->conflicts - c->trace_prev_conf, c->hctr->overflows - c->trace_prev_ovf, capC,
                 c->hctr->cav_tets - c->trace_prev_cav, c->hctr->insphere - c->trace_prev_ins);
         prev_won = c->hctr->won;
+        if (c->trace >= 2) HIPCHK(hipStreamSynchronize(c->stream));  // the balls' clocks
         if (c->trace >= 2 && max_cand && c->clk[slot] && c->clk_cap[slot] >= max_cand) trace_clocks(c, slot, max_cand);
         c->trace_prev_att = c->hctr->attempts;
         c->trace_prev_walk = c->hctr->walk_steps;
@@ -1322,6 +1330,7 @@ int insert_clouds(dt_ctx *c, const double *xyz, uint64_t n, const std::vector<ui
     if ((rc = ensure_round_buffers(c, (uint32_t)std::min<uint64_t>(want_r, std::max<uint64_t>(n, ROUND_MIN)))))
         return rc;
     rc = run_rounds(c, lv, d_start, d_size, d_bits, d_rb, base, n);
+    if (rc == DT_OK) HIPCHK(hipStreamSynchronize(c->stream));  // the last round's balls
     auto t2 = std::chrono::steady_clock::now();
     c->st.ms_sort += std::chrono::duration<double, std::milli>(t1 - t0).count();
     c->st.ms_insert += std::chrono::duration<double, std::milli>(t2 - t1).count();
@@ -1889,7 +1898,7 @@ int dt_destroy(dt_ctx *c) {
     for (int k = 0; k < 3; ++k) f(c->clk[k]);
     for (int k = 0; k < 4; ++k) { f(c->lpt[k]); f(c->lrank[k]); }
     f(c->cav); f(c->bnd); f(c->outc); f(c->cnt); f(c->status);
-    f(c->scr_v); f(c->scr_n); f(c->defer); f(c->lost);
+    f(c->scr_v); f(c->scr_n); f(c->defer); f(c->lost); f(c->wins);
     f(c->ctr);
     f(c->stat);
     if (c->hring) hipHostFree(c->hring);

@@ -1040,6 +1040,232 @@ __global__ __launch_bounds__(256) void k_cavity_b(RoundArgs a) {
     add_stat(a.stat, STAT_PERTURBED, st.perturbed);
 }
 
+// ------------------------------------------------------------------ selection and round end
+
+// a word that atomics of this kernel may have changed: past any copy in the vector L1
+template <class U>
+__device__ __forceinline__ U fresh(const U *p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// the unused part of this round's free list goes behind the slots freed this round (as far as
+// the list holds them)
+__device__ __forceinline__ void carry_free(const RoundArgs &a, uint32_t from, uint32_t step) {
+    const uint32_t fln = a.ctr->fl_n, take = fresh(&a.ctr->fl_take), nxt = min(fresh(&a.ctr->fl_next), a.flcap);
+    if (take >= fln) return;
+    const uint32_t left = min(fln - take, a.flcap - nxt);
+    for (uint32_t k = from; k < left; k += step) a.fl_next[nxt + k] = a.fl_cur[take + k];
+}
+
+__global__ void k_freelist_carry(RoundArgs a) {
+    carry_free(a, blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x);
+}
+
+// Round end, one block: the free list's rest carried, the statistics summed (one wavefront per
+// statistic), the pool's counters advanced (the ball kernel, which follows, finds what it needs
+// of the old ones beside them).  With end.snap (pinned host memory), the counters are then
+// written there and `seq` (host memory too) is set to `tag` after them with a release at system
+// scope: the host waits for that value instead of for a copy and an event.
+constexpr int ROLL_BLOCK = 1024;
+static_assert(NSTAT * 64 <= ROLL_BLOCK && STAT_SPREAD == 64, "one wavefront sums one statistic");
+
+__device__ __forceinline__ void roll_counters(const RoundArgs &a, bool carry, const RoundEnd &end) {
+    __shared__ uint32_t s_ovf;  // attempts that overflowed in this round
+    const uint32_t t = threadIdx.x;
+    Ctr *const ctr = a.ctr;
+    if (t < NSTAT * 64) {
+        unsigned long long x = fresh(&a.stat[((size_t)(t >> 6) * STAT_SPREAD + (t & 63u)) * STAT_PAD]);
+        for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
+        if ((t & 63u) == 0) {
+            const int id = (int)(t >> 6);
+            if (id == STAT_WON) {
+                ctr->won = (uint32_t)x;
+            } else if (id == STAT_WALK_CAPS) {
+                ctr->walk_caps = (uint32_t)x;
+            } else if (id == STAT_OVERFLOWS) {
+                s_ovf = (uint32_t)x - ctr->overflows;
+                ctr->overflows = (uint32_t)x;
+            } else {
+                unsigned long long *dst[STAT_WON] = {&ctr->attempts, &ctr->walk_steps, &ctr->orient, &ctr->orient_exact,
+                                                     &ctr->insphere, &ctr->insphere_exact, &ctr->perturbed,
+                                                     &ctr->cav_tets, &ctr->bnd_facets};
+                *dst[id] = x;
+            }
+        }
+    }
+    if (carry) carry_free(a, t, ROLL_BLOCK);
+    __syncthreads();
+    if (t == 0) {
+        const uint32_t fln = ctr->fl_n, take = fresh(&ctr->fl_take), freed = fresh(&ctr->fl_next);
+        const uint32_t next_n = fresh(&ctr->next_n);
+        ctr->ball_wins = fresh(&ctr->wins);
+        ctr->ball_fl_n = fln;
+        ctr->ball_tet_count = ctr->tet_count;
+        if (take > fln) {
+            // units beyond the free list were fresh pool slots (beyond the pool: never used)
+            const unsigned long long tc = (unsigned long long)ctr->tet_count + (take - fln);
+            ctr->tet_count = tc > a.tcap ? a.tcap : (uint32_t)tc;
+        }
+        const uint32_t left = take < fln ? fln - take : 0u;
+        const uint32_t nxt = min(freed, a.flcap), keep = min(left, a.flcap - nxt);
+        ctr->dropped += (freed - nxt) + (left - keep);
+        ctr->deferred += ctr->ndefer;
+        ctr->ndefer = 0;
+        ctr->fl_n = nxt + keep;
+        ctr->fl_take = 0;
+        ctr->fl_next = 0;
+        ctr->wins = 0;
+        // those that try again lost to a conflict, or (rounds over overflowed attempts, whose
+        // two lists are one) overflowed again
+        ctr->conflicts += next_n - (a.nnext_ptr == a.novf_ptr ? s_ovf : 0u);
+        *a.nnext_ptr += next_n;
+        ctr->next_n = 0;
+        *const_cast<uint32_t *>(a.ncand_ptr) = 0;  // the list this round read from is empty now
+    }
+    if (!end.snap) return;
+    __threadfence_block();
+    __syncthreads();
+    static_assert(sizeof(Ctr) % sizeof(uint32_t) == 0, "the snapshot is copied in words");
+    uint32_t *src = reinterpret_cast<uint32_t *>(ctr);
+    uint32_t *dst = reinterpret_cast<uint32_t *>(end.snap);
+    for (uint32_t k = t; k < sizeof(Ctr) / sizeof(uint32_t); k += ROLL_BLOCK) dst[k] = fresh(&src[k]);
+    __threadfence_system();
+    __syncthreads();
+    if (t == 0) __hip_atomic_store(end.seq, end.tag, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// What becomes of each attempt, one thread per attempt: winners are listed with the slots they
+// take (units below fl_n are free-list entries of earlier rounds, the rest fresh pool slots from
+// tet_count on; a ball smaller than its cavity gives slots back), and attempts that try again
+// are queued for the next round (ST_FULL: a round whose exact pass was not launched left it; in
+// rounds over overflowed attempts both lists are one).  All of a block's places come from one
+// atomic on each of two counters: atomics on one address take about 55 ns each one after the
+// other, and when every 64 attempts of the ball kernel took one, they were a third of its time.
+template <class K>
+__device__ __forceinline__ void select_attempts(const RoundArgs &a, uint32_t i) {
+    constexpr int NW = FILL_BLOCK / 64;
+    __shared__ unsigned long long s_wave[NW + 1];
+    __shared__ unsigned long long s_take;
+    __shared__ uint32_t s_win;
+    typename K::Rec *const T = static_cast<typename K::Rec *>(a.T);
+    const uint32_t lane = threadIdx.x & 63u, wid = threadIdx.x >> 6;
+    const bool any = i < *a.ncand_ptr;
+    const uint8_t status = any ? a.status[i] : (uint8_t)ST_NONE;
+    const bool cand = any && status == ST_CAND;
+    const bool win = cand && a.lost[i] != a.lost_mark;
+    uint32_t nc = 0, nb = 0;
+    if (win) {
+        nc = a.cnt[i];
+        nb = a.cnt[a.stride + i];
+    }
+    const uint32_t need = nb > nc ? nb - nc : 0u;
+    const bool ovf = any && status == ST_OVERFLOW, one_list = a.nnext_ptr == a.novf_ptr;
+    const bool again = any && (status == ST_CONFLICT || status == ST_WALK || status == ST_FULL || (cand && !win));
+    const bool listed = again || (ovf && one_list);
+    const uint32_t list0 = *a.nnext_ptr;  // advanced when the counters are rolled
+    // per block at most 1024 winners and listed attempts
+    const unsigned long long mine = ((unsigned long long)need << 22) | ((unsigned long long)listed << 11) | (win ? 1u : 0u);
+    unsigned long long x = mine;
+    for (int o = 1; o < 64; o <<= 1) {
+        const unsigned long long y = __shfl_up(x, o, 64);
+        if (lane >= (uint32_t)o) x += y;
+    }
+    if (lane == 63) s_wave[wid] = x;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        unsigned long long t = 0;
+        for (int w = 0; w < NW; ++w) {
+            const unsigned long long c = s_wave[w];
+            s_wave[w] = t;
+            t += c;
+        }
+        const unsigned long long take = (t >> 22) | ((t >> 11 & 0x7FFull) << 32);
+        s_take = take ? atomicAdd(reinterpret_cast<unsigned long long *>(&a.ctr->fl_take), take) : 0ull;
+        s_win = t & 0x7FFull ? atomicAdd(&a.ctr->wins, (uint32_t)(t & 0x7FFull)) : 0u;
+    }
+    __syncthreads();
+    const unsigned long long before = s_wave[wid] + x - mine;
+    uint32_t u0 = (uint32_t)s_take + (uint32_t)(before >> 22);
+    if (listed) {
+        const uint32_t at = list0 + (uint32_t)(s_take >> 32) + (uint32_t)(before >> 11 & 0x7FFull);
+        a.next_pt[at] = a.cand_pt[i];
+        a.next_rank[at] = a.cand_rank[i];
+    }
+    if (ovf && !one_list) {
+        const uint32_t at = atomicAdd(a.novf_ptr, 1u);
+        a.ovf_pt[at] = a.cand_pt[i];
+        a.ovf_rank[at] = a.cand_rank[i];
+    }
+    bool built = win;
+    const uint32_t fln = a.ctr->fl_n, tc0 = a.ctr->tet_count;
+    if (need && u0 + need > fln && (uint64_t)tc0 + (u0 + need - fln) > a.tcap) {
+        // pool full: give the units back (pool slots inside the pool are marked free) and
+        // retry next round after the host has grown the pool
+        built = false;
+        uint32_t give = 0;
+        for (uint32_t k = 0; k < need; ++k) {
+            const uint32_t u = u0 + k;
+            if (u < fln || (uint64_t)tc0 + (u - fln) < a.tcap) ++give;
+        }
+        const uint32_t g0 = atomicAdd(&a.ctr->fl_next, give);
+        uint32_t q = 0;
+        for (uint32_t k = 0; k < need; ++k) {
+            const uint32_t u = u0 + k;
+            uint32_t slot = NONE;
+            if (u < fln) {
+                slot = a.fl_cur[u];
+            } else if ((uint64_t)tc0 + (u - fln) < a.tcap) {
+                slot = tc0 + (u - fln);
+                T[slot].v.x = DEAD;
+            }
+            // a slot that does not fit the free list stays free and unused (k_roll counts it)
+            if (slot != NONE && (uint64_t)g0 + q < a.flcap) a.fl_next[g0 + q] = slot;
+            if (slot != NONE) ++q;
+        }
+        atomicOr(&a.ctr->error, ERR_POOL);
+        const uint32_t at = list0 + atomicAdd(&a.ctr->next_n, 1u);
+        a.next_pt[at] = a.cand_pt[i];
+        a.next_rank[at] = a.cand_rank[i];
+    }
+    if (built && nc > nb) u0 = atomicAdd(&a.ctr->fl_next, nc - nb);  // rare
+    if (win) a.wins[s_win + (uint32_t)(before & 0x7FFull)] = make_uint2(built ? i : NONE, u0);
+    if (any && (status == ST_NONE || status == ST_ERROR)) atomicOr(&a.ctr->error, ERR_WALK);
+    if (a.log_att && any) atomicAdd(&a.log_att[a.cand_pt[i] - a.vlo], 1u);
+    add_stat(a.stat, STAT_CAV_TETS, built ? nc : 0u);
+    add_stat(a.stat, STAT_BND_FACETS, built ? nb : 0u);
+    add_count(a.stat, STAT_WON, built);
+    add_count(a.stat, STAT_OVERFLOWS, ovf);
+    add_count(a.stat, STAT_WALK_CAPS, any && status == ST_WALK);
+}
+
+template <class K>
+__global__ __launch_bounds__(FILL_BLOCK) void k_select(RoundArgs a) {
+    select_attempts<K>(a, blockIdx.x * FILL_BLOCK + threadIdx.x);
+}
+
+__global__ __launch_bounds__(ROLL_BLOCK) void k_roll(RoundArgs a, uint32_t carry, RoundEnd end) {
+    roll_counters(a, carry != 0, end);
+}
+
+// Both in one launch, one block, for short rounds: a launch and its gap take about 7 us, a pass
+// over 1024 attempts about 2.
+constexpr uint32_t SELECT_ONE_BLOCK = 4096;
+static_assert(FILL_BLOCK == ROLL_BLOCK, "one block does both");
+
+template <class K>
+__global__ __launch_bounds__(ROLL_BLOCK) void k_select_roll(RoundArgs a, uint32_t carry, RoundEnd end) {
+    const uint32_t n = *a.ncand_ptr;
+    for (uint32_t i0 = 0; i0 < n; i0 += ROLL_BLOCK) {
+        select_attempts<K>(a, i0 + threadIdx.x);
+        __syncthreads();
+    }
+    __threadfence_block();  // this wave's atomics have been performed
+    __syncthreads();
+    roll_counters(a, carry != 0, end);
+}
+
+// ------------------------------------------------------------------ DelaunayBall
+
 // Winner test, slot reservation and DelaunayBall (Sec. 2.5), GL lanes per candidate, all in
 // one wave.  An attempt wins iff it completed its cavity and is not marked as lost (see the
 // head of this file); winners have disjoint cavities and no cavity meets another winner's
@@ -1063,7 +1289,7 @@ constexpr uint32_t HT_MAX_FACETS = 64;   // balls up to this size use the table 
 constexpr unsigned long long HT_EMPTY = ~0ull;
 // threads per block of the ball kernel: the slot reservation is one atomic per block on one
 // counter, so larger blocks contend less (at the cost of LDS occupancy)
-constexpr int BALL_BLOCK = 1024;
+constexpr int BALL_BLOCK = 256;
 
 // orders the memory accesses of one group (all in one wave) across phases
 __device__ __forceinline__ void group_fence() {
@@ -1105,80 +1331,23 @@ __global__ __launch_bounds__(BS) void k_ball(RoundArgs a) {
     const uint32_t gi = threadIdx.x / GL;
     const uint32_t gbase = lane & ~(uint32_t)(GL - 1);
     const unsigned long long gmask = GL == 64 ? ~0ull : (((1ull << (GL & 63)) - 1ull) << gbase);
-    const uint32_t i = blockIdx.x * GPB + gi;
-    const uint32_t ncand = *a.ncand_ptr;
-    const uint32_t stride = a.stride, capC = a.capC, capF = a.capF;
-    unsigned cav_w = 0, bnd_w = 0;
+    const uint32_t wi = blockIdx.x * GPB + gi;
+    if (wi >= a.ctr->ball_wins) return;  // whole groups; no barrier below
     const unsigned long long tb0 = a.clk ? (unsigned long long)wall_clock64() : 0ull;
-    const uint8_t status = i < ncand ? a.status[i] : (uint8_t)ST_NONE;
-    const bool cand = status == ST_CAND;
-    uint32_t p = 0, nc = 0, nb = 0;
-    unsigned long long S = 0;
+    const uint2 rec = a.wins[wi];
+    const uint32_t i = rec.x, u0 = rec.y;
+    if (i == NONE) return;  // the pool had no room for it
+    const uint32_t capC = a.capC, capF = a.capF;
     const code *cavl = static_cast<const code *>(a.cav) + (size_t)i * capC;
     const uint32_t *bl = a.bnd + (size_t)i * capF;
     code *ol = static_cast<code *>(a.outc) + (size_t)i * capF;
     uint4 *sv = a.scr_v + (size_t)i * capC;
     typename K::code4 *sn = static_cast<typename K::code4 *>(a.scr_n) + (size_t)i * capC;
-    if (cand) {
-        p = a.cand_pt[i];
-        S = claim_stamp(a, i);
-        nc = a.cnt[i];
-        nb = a.cnt[stride + i];
-    }
-    const bool win = cand && a.lost[i] != a.lost_mark;
-    // What each attempt takes, by its first lane, with one atomic per block on one counter:
-    // slots for a winner (units below fl_n are free-list entries of earlier rounds, the rest
-    // fresh pool slots from tet_count on; C - F surplus cavity slots are freed), a place in the
-    // next list for an attempt that tries again (ST_FULL: a round whose exact pass was not
-    // launched left it).  In rounds over overflowed attempts both lists are one.
-    const bool first = gl == 0, leader = win && first;
-    const uint32_t need = leader && nb > nc ? nb - nc : 0u;
-    const bool ovf = first && status == ST_OVERFLOW, one_list = a.nnext_ptr == a.novf_ptr;
-    const bool again = first && (status == ST_CONFLICT || status == ST_WALK || status == ST_FULL || (cand && !win));
-    const bool listed = again || (ovf && one_list);
-    const uint32_t list0 = *a.nnext_ptr;  // advanced at the round's end
-    const unsigned long long took =
-        block_reserve<BS / 64, unsigned long long>(need | ((unsigned long long)listed << 32),
-                                                   reinterpret_cast<unsigned long long *>(&a.ctr->fl_take),
-                                                   &s_key[0][0]);
-    const uint32_t u0 = (uint32_t)took;
-    const uint32_t fln = a.ctr->fl_n, tc0 = a.ctr->tet_count;
-    const bool full = need && u0 + need > fln && (uint64_t)tc0 + (u0 + need - fln) > a.tcap;
-    if (full) {
-        // pool full: give the units back (pool slots inside the pool are marked free) and
-        // retry next round after the host has grown the pool
-        uint32_t give = 0;
-        for (uint32_t k = 0; k < need; ++k) {
-            const uint32_t u = u0 + k;
-            if (u < fln || (uint64_t)tc0 + (u - fln) < a.tcap) ++give;
-        }
-        const uint32_t g0 = atomicAdd(&a.ctr->fl_next, give);
-        uint32_t q = 0;
-        for (uint32_t k = 0; k < need; ++k) {
-            const uint32_t u = u0 + k;
-            uint32_t slot = NONE;
-            if (u < fln) {
-                slot = a.fl_cur[u];
-            } else if ((uint64_t)tc0 + (u - fln) < a.tcap) {
-                slot = tc0 + (u - fln);
-                T[slot].v.x = DEAD;
-            }
-            // a slot that does not fit the free list stays free and unused (k_roll counts it)
-            if (slot != NONE && (uint64_t)g0 + q < a.flcap) a.fl_next[g0 + q] = slot;
-            if (slot != NONE) ++q;
-        }
-        atomicOr(&a.ctr->error, ERR_POOL);
-        const uint32_t at = list0 + atomicAdd(&a.ctr->next_n, 1u);
-        a.next_pt[at] = p;
-        a.next_rank[at] = a.cand_rank[i];
-    }
-    const bool lbuilt = leader && !full;
-    const uint32_t fb = lbuilt && nc > nb ? atomicAdd(&a.ctr->fl_next, nc - nb) : 0u;  // rare
-    const bool built = __shfl((int)lbuilt, (int)gbase) != 0;
-    const uint32_t g_u0 = __shfl(u0, (int)gbase), g_fb = __shfl(fb, (int)gbase);
+    const uint32_t p = a.cand_pt[i], nc = a.cnt[i], nb = a.cnt[a.stride + i];
+    const uint32_t fln = a.ctr->ball_fl_n, tc0 = a.ctr->ball_tet_count;
     const unsigned long long tb1 = a.clk ? (unsigned long long)wall_clock64() : 0ull;
     unsigned long long tb2 = tb1;
-    if (built && nb <= HT_MAX_FACETS) {
+    if (nb <= HT_MAX_FACETS) {
         // Balls of up to HT_MAX_FACETS facets: lane gl builds the tetrahedra on boundary facets
         // gl, gl + GL, ... from registers.  Everything read from the cavity is read before the
         // first store into it.
@@ -1198,7 +1367,7 @@ __global__ __launch_bounds__(BS) void k_ball(RoundArgs a) {
                 if (b < nc) {
                     slot[k] = code_slot(cavl[b]);
                 } else {
-                    const uint32_t u = g_u0 + (b - nc);
+                    const uint32_t u = u0 + (b - nc);
                     slot[k] = u < fln ? a.fl_cur[u] : tc0 + (u - fln);
                 }
             }
@@ -1287,7 +1456,7 @@ __global__ __launch_bounds__(BS) void k_ball(RoundArgs a) {
                 }
             }
         }
-    } else if (built) {
+    } else {
         // Larger balls: siblings by pivoting around each edge through copies of the cavity
         // tetrahedra (vertices, neighbours, and the local index in the spare word)
         for (uint32_t k = gl; k < nc; k += GL) {
@@ -1304,7 +1473,7 @@ __global__ __launch_bounds__(BS) void k_ball(RoundArgs a) {
             const int f = (int)(task & 3u);
             const code cd = comp(sn[k], f);
             const uint32_t nt = code_slot(cd);
-            if (T[nt].claim == S)  // only this winner's cavity tetrahedra hold S
+            if (T[nt].claim == claim_stamp(a, i))  // only this winner's cavity tetrahedra hold S
                 reinterpret_cast<code *>(&sn[k])[f] = make_code<K>((uint32_t)T[nt].spare[0], code_facet(cd));
         }
         group_fence();
@@ -1314,7 +1483,7 @@ __global__ __launch_bounds__(BS) void k_ball(RoundArgs a) {
             if (b < nc) {
                 slot = code_slot(cavl[b]);
             } else {
-                const uint32_t u = g_u0 + (b - nc);
+                const uint32_t u = u0 + (b - nc);
                 slot = u < fln ? a.fl_cur[u] : tc0 + (u - fln);
             }
             const uint32_t bc = bl[b];  // local index of the cavity tetrahedron << 2 | facet
@@ -1380,137 +1549,28 @@ __global__ __launch_bounds__(BS) void k_ball(RoundArgs a) {
             else nref(T, slot, q) = res;
         }
     }
-    if (built) {
-        // E: cavity slots beyond the ball's size are freed.  The cloud's known live
-        // tetrahedron stays live unless it is one of them (the other cavity slots hold the
-        // new tetrahedra): then it moves to the ball's first tetrahedron.  Only this rare
-        // case writes it, so winners do not all store to one address.
-        if (nc > nb) {
-            Cloud *cl = &a.clouds[a.V[p].idx >> 32];
-            const uint32_t live = cl->any_live;
-            for (uint32_t k = nb + gl; k < nc; k += GL) {
-                const uint32_t c = code_slot(cavl[k]);
-                T[c].v.x = DEAD;
-                // a slot that does not fit the free list stays free and unused (k_roll counts it)
-                if ((uint64_t)g_fb + (k - nb) < a.flcap) a.fl_next[g_fb + (k - nb)] = c;
-                if (c == live) cl->any_live = code_slot(cavl[0]);
-            }
-        }
-        if (gl == 0) {
-            cav_w = nc;
-            bnd_w = nb;
+    // Cavity slots beyond the ball's size are freed.  The cloud's known live tetrahedron stays
+    // live unless it is one of them (the other cavity slots hold the new tetrahedra): then it
+    // moves to the ball's first tetrahedron.  Only this rare case writes it, so winners do not
+    // all store to one address.
+    if (nc > nb) {
+        Cloud *cl = &a.clouds[a.V[p].idx >> 32];
+        const uint32_t live = cl->any_live;
+        for (uint32_t k = nb + gl; k < nc; k += GL) {
+            const uint32_t c = code_slot(cavl[k]);
+            T[c].v.x = DEAD;
+            // a slot that does not fit the free list stays free and unused (k_roll counts it)
+            if ((uint64_t)u0 + (k - nb) < a.flcap) a.fl_next[u0 + (k - nb)] = c;
+            if (c == live) cl->any_live = code_slot(cavl[0]);
         }
     }
-    if (a.clk && cand && gl == 0) {
+    if (a.clk && gl == 0) {
         unsigned long long *r = a.clk + 8ull * i + 4;
         r[0] = tb0;
         r[1] = tb1;
-        r[2] = built ? tb2 : 0ull;
-        r[3] = built ? (unsigned long long)wall_clock64() : 0ull;
+        r[2] = tb2;
+        r[3] = (unsigned long long)wall_clock64();
     }
-    // the lists, behind the building: no winner waits for these loads
-    if (listed) {
-        const uint32_t at = list0 + (uint32_t)(took >> 32);
-        a.next_pt[at] = a.cand_pt[i];
-        a.next_rank[at] = a.cand_rank[i];
-    }
-    if (ovf && !one_list) {
-        const uint32_t at = atomicAdd(a.novf_ptr, 1u);
-        a.ovf_pt[at] = a.cand_pt[i];
-        a.ovf_rank[at] = a.cand_rank[i];
-    }
-    if (first && i < ncand && (status == ST_NONE || status == ST_ERROR)) atomicOr(&a.ctr->error, ERR_WALK);
-    if (a.log_att && first && i < ncand) atomicAdd(&a.log_att[a.cand_pt[i] - a.vlo], 1u);
-    add_stat(a.stat, STAT_CAV_TETS, cav_w);
-    add_stat(a.stat, STAT_BND_FACETS, bnd_w);
-    add_count(a.stat, STAT_WON, lbuilt);
-    add_count(a.stat, STAT_OVERFLOWS, ovf);
-    add_count(a.stat, STAT_WALK_CAPS, first && status == ST_WALK);
-}
-
-// ------------------------------------------------------------------ round end
-
-// the unused part of this round's free list goes behind the slots freed this round (as far as
-// the list holds them)
-__device__ __forceinline__ void carry_free(const RoundArgs &a, uint32_t from, uint32_t step) {
-    const uint32_t fln = a.ctr->fl_n, take = a.ctr->fl_take, nxt = min(a.ctr->fl_next, a.flcap);
-    if (take >= fln) return;
-    const uint32_t left = min(fln - take, a.flcap - nxt);
-    for (uint32_t k = from; k < left; k += step) a.fl_next[nxt + k] = a.fl_cur[take + k];
-}
-
-__global__ void k_freelist_carry(RoundArgs a) {
-    carry_free(a, blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x);
-}
-
-// Round end, one block: the free list's rest carried, the statistics summed (one wavefront per
-// statistic), the pool's counters advanced.  The ball kernel has queued the attempts that try
-// again; a round thus ends with one launch of about 5 us (a compaction, a carry and a roll
-// kernel took 16).  With `snap` (pinned host memory), the counters are then written there and
-// `seq` (host memory too) is set to `tag` after them with a release at system scope: the host
-// waits for that value instead of for a copy and an event.
-constexpr int ROLL_BLOCK = 1024;
-static_assert(NSTAT * 64 <= ROLL_BLOCK && STAT_SPREAD == 64, "one wavefront sums one statistic");
-
-__global__ __launch_bounds__(ROLL_BLOCK) void k_roll(RoundArgs a, uint32_t *consumed, uint32_t carry, Ctr *snap,
-                                                     unsigned long long *seq, unsigned long long tag) {
-    __shared__ uint32_t s_ovf;  // attempts that overflowed in this round
-    const uint32_t t = threadIdx.x;
-    Ctr *const ctr = a.ctr;
-    if (t < NSTAT * 64) {
-        unsigned long long x = a.stat[((size_t)(t >> 6) * STAT_SPREAD + (t & 63u)) * STAT_PAD];
-        for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
-        if ((t & 63u) == 0) {
-            const int id = (int)(t >> 6);
-            if (id == STAT_WON) {
-                ctr->won = (uint32_t)x;
-            } else if (id == STAT_WALK_CAPS) {
-                ctr->walk_caps = (uint32_t)x;
-            } else if (id == STAT_OVERFLOWS) {
-                s_ovf = (uint32_t)x - ctr->overflows;
-                ctr->overflows = (uint32_t)x;
-            } else {
-                unsigned long long *dst[STAT_WON] = {&ctr->attempts, &ctr->walk_steps, &ctr->orient, &ctr->orient_exact,
-                                                     &ctr->insphere, &ctr->insphere_exact, &ctr->perturbed,
-                                                     &ctr->cav_tets, &ctr->bnd_facets};
-                *dst[id] = x;
-            }
-        }
-    }
-    if (carry) carry_free(a, t, ROLL_BLOCK);
-    __syncthreads();
-    if (t == 0) {
-        const uint32_t fln = ctr->fl_n, take = ctr->fl_take;
-        if (take > fln) {
-            // units beyond the free list were fresh pool slots (beyond the pool: never used)
-            const unsigned long long tc = (unsigned long long)ctr->tet_count + (take - fln);
-            ctr->tet_count = tc > a.tcap ? a.tcap : (uint32_t)tc;
-        }
-        const uint32_t left = take < fln ? fln - take : 0u;
-        const uint32_t nxt = min(ctr->fl_next, a.flcap), keep = min(left, a.flcap - nxt);
-        ctr->dropped += (ctr->fl_next - nxt) + (left - keep);
-        ctr->deferred += ctr->ndefer;
-        ctr->ndefer = 0;
-        ctr->fl_n = nxt + keep;
-        ctr->fl_take = 0;
-        ctr->fl_next = 0;
-        // those that try again lost to a conflict, or (rounds over overflowed attempts, whose
-        // two lists are one) overflowed again
-        ctr->conflicts += ctr->next_n - (a.nnext_ptr == a.novf_ptr ? s_ovf : 0u);
-        *a.nnext_ptr += ctr->next_n;
-        ctr->next_n = 0;
-        *consumed = 0;  // the list this round read from is empty now
-    }
-    if (!snap) return;
-    __threadfence_block();
-    __syncthreads();
-    static_assert(sizeof(Ctr) % sizeof(uint32_t) == 0, "the snapshot is copied in words");
-    const uint32_t *src = reinterpret_cast<const uint32_t *>(ctr);
-    uint32_t *dst = reinterpret_cast<uint32_t *>(snap);
-    for (uint32_t k = t; k < sizeof(Ctr) / sizeof(uint32_t); k += ROLL_BLOCK) dst[k] = src[k];
-    __threadfence_system();
-    __syncthreads();
-    if (t == 0) __hip_atomic_store(seq, tag, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // The exact-predicate pass: 16 lanes per attempt (its attempts are whole walks and cavity
@@ -1521,7 +1581,7 @@ constexpr uint32_t DEFER_BLOCKS = 1024;
 
 template <class K>
 static hipError_t launch_round_k(const RoundArgs &a, uint32_t max_cand, uint32_t lanes, uint32_t large_lanes,
-                                 bool exact, hipStream_t s, hipEvent_t *ev) {
+                                 bool exact, const RoundEnd &end, hipStream_t s, hipEvent_t *ev) {
     if (ev) hipEventRecord(ev[0], s);
     // regular rounds: the filter-only kernel over the round's list, then the exact kernel over
     // the attempts it handed on (a short grid-stride pass; nothing to do for most rounds);
@@ -1558,6 +1618,14 @@ static hipError_t launch_round_k(const RoundArgs &a, uint32_t max_cand, uint32_t
         if (exact) k_cavity_g<K, EXACT_LANES, LCAPC, LHM, false, true, true><<<dgrid, 256, 0, s>>>(a);
     }
     if (ev) hipEventRecord(ev[1], s);
+    const bool apart = end.free_slots > ROLL_CARRY;
+    if (max_cand <= SELECT_ONE_BLOCK && !apart) {
+        k_select_roll<K><<<1, ROLL_BLOCK, 0, s>>>(a, 1u, end);
+    } else {
+        k_select<K><<<(max_cand + FILL_BLOCK - 1) / FILL_BLOCK, FILL_BLOCK, 0, s>>>(a);
+        if (apart) k_freelist_carry<<<256, 256, 0, s>>>(a);
+        k_roll<<<1, ROLL_BLOCK, 0, s>>>(a, apart ? 0u : 1u, end);
+    }
     // rounds for large cavities build large balls (their siblings found by pivoting), and
     // short rounds wait on their slowest candidate: a wavefront per candidate
     if (a.capC > LCAPC || lanes == 64)
@@ -1569,18 +1637,13 @@ static hipError_t launch_round_k(const RoundArgs &a, uint32_t max_cand, uint32_t
 }
 
 hipError_t launch_round(const RoundArgs &a, bool wide, uint32_t max_cand, uint32_t lanes, uint32_t large_lanes,
-                        bool exact, hipStream_t s, hipEvent_t *ev) {
-    if (max_cand == 0) return hipSuccess;
-    return wide ? launch_round_k<Wide>(a, max_cand, lanes, large_lanes, exact, s, ev)
-                : launch_round_k<Narrow>(a, max_cand, lanes, large_lanes, exact, s, ev);
-}
-
-hipError_t launch_round_end(const RoundArgs &a, uint32_t free_slots, hipStream_t s, Ctr *snap,
-                            unsigned long long *seq, unsigned long long tag) {
-    const bool apart = free_slots > ROLL_CARRY;
-    if (apart) k_freelist_carry<<<256, 256, 0, s>>>(a);
-    k_roll<<<1, ROLL_BLOCK, 0, s>>>(a, const_cast<uint32_t *>(a.ncand_ptr), apart ? 0u : 1u, snap, seq, tag);
-    return hipGetLastError();
+                        bool exact, const RoundEnd &end, hipStream_t s, hipEvent_t *ev) {
+    if (max_cand == 0) {
+        k_roll<<<1, ROLL_BLOCK, 0, s>>>(a, 1u, end);
+        return hipGetLastError();
+    }
+    return wide ? launch_round_k<Wide>(a, max_cand, lanes, large_lanes, exact, end, s, ev)
+                : launch_round_k<Narrow>(a, max_cand, lanes, large_lanes, exact, end, s, ev);
 }
 
 // ------------------------------------------------------------------ graph-launched rounds
@@ -1610,11 +1673,9 @@ int lanes_index(uint32_t lanes) {
 
 }  // namespace
 
-// The kernels and grids are those of launch_fill_list, launch_round (regular rounds) and
-// launch_round_end; an empty fill plan runs one block that appends nothing.
+// The kernels and grids are those of launch_fill_list and launch_round (regular rounds); an empty fill plan runs one block that appends nothing.
 hipError_t launch_round_graph(RoundGraph *graphs, const FillPlan &plan, const FillArgs &fa, const RoundArgs &a,
-                              bool wide, uint32_t max_cand, uint32_t lanes, Ctr *snap, unsigned long long *seq,
-                              unsigned long long tag, hipStream_t s) {
+                              bool wide, uint32_t max_cand, uint32_t lanes, const RoundEnd &end, hipStream_t s) {
     if (max_cand == 0 || a.capC > LCAPC) return hipErrorInvalidValue;
     const uint32_t L = lanes == 4 || lanes == 8 || lanes == 32 || lanes == 64 ? lanes : 16u;
     RoundGraph &g = graphs[(wide ? 5 : 0) + lanes_index(L)];
@@ -1629,12 +1690,12 @@ hipError_t launch_round_graph(RoundGraph *graphs, const FillPlan &plan, const Fi
     FillPlan pl = plan;
     FillArgs f = fa;
     RoundArgs ra = a;
-    uint32_t *consumed = const_cast<uint32_t *>(a.ncand_ptr);
     uint32_t carry = 1;
+    RoundEnd re = end;
     void *fill_args[] = {&pl, &f.lvl_start, &f.lvl_size, &f.lvl_bits, &f.rank_base, &f.lord, &f.dup, &f.vtet,
                          &f.cand_pt, &f.cand_rank, &f.ncand};
     void *round_args[] = {&ra};
-    void *roll_args[] = {&ra, &consumed, &carry, &snap, &seq, &tag};
+    void *roll_args[] = {&ra, &carry, &re};
     hipKernelNodeParams p[ROUND_GRAPH_NODES] = {};
     auto set = [&](int k, void *fn, uint32_t grid, uint32_t block, void **args) {
         p[k].func = fn;
@@ -1648,7 +1709,9 @@ hipError_t launch_round_graph(RoundGraph *graphs, const FillPlan &plan, const Fi
     set(0, (void *)k_fill, (fill_count + FILL_BLOCK - 1) / FILL_BLOCK, FILL_BLOCK, fill_args);
     set(1, k_cav, (max_cand + gpb - 1) / gpb, 256, round_args);
     set(2, k_exact, std::min<uint32_t>((max_cand + 256 / EXACT_LANES - 1) / (256 / EXACT_LANES), DEFER_BLOCKS), 256, round_args);
-    set(3, k_b, (max_cand + BALL_BLOCK / gl_ball - 1) / (BALL_BLOCK / gl_ball), BALL_BLOCK, round_args);
+    set(3, wide ? (void *)k_select<Wide> : (void *)k_select<Narrow>, (max_cand + FILL_BLOCK - 1) / FILL_BLOCK,
+        FILL_BLOCK, round_args);
+    set(5, k_b, (max_cand + BALL_BLOCK / gl_ball - 1) / (BALL_BLOCK / gl_ball), BALL_BLOCK, round_args);
     set(4, (void *)k_roll, 1, ROLL_BLOCK, roll_args);
     hipError_t e;
     if (!g.exec) {

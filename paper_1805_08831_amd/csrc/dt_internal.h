@@ -102,7 +102,10 @@ struct Ctr {
     uint32_t list_count[4];  // lengths of the candidate lists (two normal, two overflow)
     uint32_t fl_n;       // free slots available this round
     uint32_t fl_next;    // slots freed this round
-    // one 64-bit counter for the ball kernel's blocks:
+    uint32_t wins;       // attempts that build their balls this round
+    // what the ball kernel needs of the round after the counters have been rolled
+    uint32_t ball_wins, ball_fl_n, ball_tet_count;
+    // one 64-bit counter for the selection kernel's blocks:
     alignas(8) uint32_t fl_take;  // slot units taken this round: unit u < fl_n is free-list entry u,
                          // unit u >= fl_n is pool slot tet_count + (u - fl_n)
     uint32_t next_n;     // candidates this round adds to the next list
@@ -180,6 +183,8 @@ struct RoundArgs {
     void *outc;                  // [stride][capF] outer codes, then new tetrahedra
     uint32_t *cnt;               // [2][stride] cavity size, boundary size
     uint8_t *status;             // [stride]
+    uint2 *wins;                 // [stride] the round's winners: attempt, first slot unit (or
+                                 // free-list place of the first surplus slot)
     uint32_t *lost;              // [stride] lost_mark where a claim of the attempt was displaced
     uint4 *scr_v;                // [stride][capC] vertex copies of the winners' cavity tetrahedra
     void *scr_n;                 // [stride][capC] their neighbour codes (pivoting balls)
@@ -289,18 +294,23 @@ hipError_t launch_fill_list(const FillPlan &plan, const uint32_t *lvl_start, con
                             const uint32_t *lvl_bits, const unsigned long long *rank_base, const uint32_t *lord,
                             const uint8_t *dup, const uint32_t *vtet, uint32_t *cand_pt, uint32_t *cand_rank,
                             uint32_t *ncand, hipStream_t s);
+// Where the round's counters go (pinned host memory; snap may be null), and the free list's
+// length as far as the host knows it (it only chooses the launches): above ROLL_CARRY entries
+// the rest of the list is carried by a kernel of its own, not by the one block of the round end.
+constexpr uint32_t ROLL_CARRY = 1u << 16;
+struct RoundEnd {
+    Ctr *snap;
+    unsigned long long *seq, tag;
+    uint32_t free_slots;
+};
+// The kernels of a round: cavity passes, selection, round end (the counters are final before the
+// balls are built, so that the host plans on while they are), DelaunayBall.
 // exact: launch the exact-predicate pass after the filter pass of a regular round (without
 // it, attempts the filter hands on retry in the next round)
 hipError_t launch_round(const RoundArgs &a, bool wide, uint32_t max_cand, uint32_t lanes, uint32_t large_lanes,
-                        bool exact, hipStream_t s, hipEvent_t *ev);
-// Free-list entries the round-end kernel's one block carries; a longer rest is carried by a
-// kernel of its own, which is launched while the host sees more of them.
-constexpr uint32_t ROLL_CARRY = 1u << 16;
-// free_slots: the free list's length as far as the host knows it (it only chooses the launches)
-hipError_t launch_round_end(const RoundArgs &a, uint32_t free_slots, hipStream_t s, Ctr *snap,
-                            unsigned long long *seq, unsigned long long tag);
+                        bool exact, const RoundEnd &end, hipStream_t s, hipEvent_t *ev);
 // A regular round (cavity buffers of the regular size) as one HIP graph: the fill, the two
-// cavity passes, the DelaunayBall kernel and the round-end kernel as a chain of kernel
+// cavity passes, the selection, DelaunayBall and round-end kernels as a chain of kernel
 // nodes.  The graph is built and instantiated once per launch shape (pool layout, lanes per
 // insertion); each later round of that shape only updates the nodes' arguments and grids.
 struct FillArgs {
@@ -311,7 +321,7 @@ struct FillArgs {
     const uint32_t *vtet;
     uint32_t *cand_pt, *cand_rank, *ncand;
 };
-constexpr int ROUND_GRAPH_NODES = 5;
+constexpr int ROUND_GRAPH_NODES = 6;
 struct RoundGraph {
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
@@ -319,8 +329,7 @@ struct RoundGraph {
 };
 constexpr int ROUND_GRAPH_SHAPES = 10;  // pool layout (2) x lanes per insertion (4, 8, 16, 32, 64)
 hipError_t launch_round_graph(RoundGraph *graphs, const FillPlan &plan, const FillArgs &fa, const RoundArgs &a,
-                              bool wide, uint32_t max_cand, uint32_t lanes, Ctr *snap, unsigned long long *seq,
-                              unsigned long long tag, hipStream_t s);
+                              bool wide, uint32_t max_cand, uint32_t lanes, const RoundEnd &end, hipStream_t s);
 void destroy_round_graphs(RoundGraph *graphs);
 hipError_t launch_reset_claims(void *T, bool wide, uint32_t tcap, hipStream_t s);
 // copies `count` Tet records into TetW records
