@@ -183,6 +183,10 @@ struct dt_ctx {
     uint32_t nclouds = 0;
     bool batch = false;                  // the context holds a dt_insert_batch result
     DevBuf<Cloud> clouds;
+    // records and grid of each insertion call so far (single clouds): walk starts of later calls
+    DevBuf<Cloud> past;
+    std::vector<uint64_t> past_size;
+    bool near_anchor = false;            // of the current call: see RoundArgs
     DevBuf<uint64_t> off, ch_start, ch_end;
     DevBuf<uint32_t> cloud_ch;
     DevBuf<double> partial;
@@ -553,6 +557,7 @@ int enqueue_round(dt_ctx *c, int ci, int ni, int oi, uint32_t max_cand, uint32_t
     a.clouds = c->clouds.p;
     a.log_att = c->logged ? c->log_att.p : nullptr;
     a.wbucket = c->learned_active ? c->wbucket.p : nullptr;
+    a.near_anchor = c->near_anchor ? 1u : 0u;
     a.cand_pt = c->lpt[ci] + off;
     a.cand_rank = c->lrank[ci] + off;
     a.next_pt = c->lpt[ni];
@@ -1212,8 +1217,23 @@ int insert_clouds(dt_ctx *c, const double *xyz, uint64_t n, const std::vector<ui
     unsigned long long *d_rb;
     if ((rc = upload_levels(c, lv, &d_start, &d_size, &d_bits, &d_rb))) return rc;
     HIPCHK(launch_anchor(lord, d_start, L, c->V.p, base, n, c->anchor.p, c->stream));
+    // an appended call finds its walk starts among the vertices of the largest earlier call; where
+    // the earlier points are at least half as many as the call's own, its walks start there at
+    // once, as those of refinement candidates at their tetrahedra
+    if (!fresh && !hint && !c->past_size.empty()) {
+        const size_t k = (size_t)(std::max_element(c->past_size.begin(), c->past_size.end()) - c->past_size.begin());
+        HIPCHK(launch_append_anchor(c->V.p, base, n, c->past.p + k, c->vtet.p, c->anchor.p, c->stream));
+    }
+    c->near_anchor = hint || (!fresh && 2 * base >= n);
     if (hint) HIPCHK(launch_hint_anchor(c->V.p, base, n, c->npoints, hint, c->anchor.p, c->stream));
     HIPCHK(hipMemsetAsync(c->lastt.p, 0xFF, n * sizeof(uint32_t), c->stream));
+    if (C == 1 && !c->arena) {
+        // this call's records and grid, for the calls after it
+        if ((rc = ensure(c, c->past, std::max<size_t>(c->past_size.size() + 1, 64), true))) return rc;
+        HIPCHK(hipMemcpyAsync(c->past.p + c->past_size.size(), c->clouds.p, sizeof(Cloud), hipMemcpyDeviceToDevice,
+                              c->stream));
+        c->past_size.push_back(n);
+    }
     c->call_clouds = C;
     c->lord = lord;
     c->exact_needed = false;
@@ -1878,6 +1898,7 @@ int dt_clear(dt_ctx *c) {
     c->hctr = c->hring;
     c->grow_pending = false;
     c->npoints = c->nv = 0;
+    c->past_size.clear();
     c->have_mesh = false;
     c->mesh_vertices = 0;
     c->fl_idx = c->list_idx = c->ovf_idx = 0;
@@ -1904,7 +1925,7 @@ int dt_destroy(dt_ctx *c) {
     if (c->hring) hipHostFree(c->hring);
     f(c->staging.p); f(c->keys.p); f(c->keys_tmp.p); f(c->table.p); f(c->vals.p); f(c->vals_tmp.p);
     f(c->hist.p); f(c->scan_tmp.p); f(c->small.p); f(c->small64.p);
-    f(c->clouds.p); f(c->off.p); f(c->ch_start.p); f(c->ch_end.p); f(c->cloud_ch.p); f(c->partial.p);
+    f(c->clouds.p); f(c->past.p); f(c->off.p); f(c->ch_start.p); f(c->ch_end.p); f(c->cloud_ch.p); f(c->partial.p);
     f(c->okeys.p); f(c->osorted.p); f(c->omap2.p); f(c->dbgV.p); f(c->dbg_cloud.p);
     f(c->lev.p); f(c->wbucket.p); f(c->log_att.p); f(c->feat.p); f(c->ypred.p);
     f(c->w32.p); f(c->m1.p); f(c->m2.p); f(c->grad.p); f(c->loss.p); f(c->wbf.p);
