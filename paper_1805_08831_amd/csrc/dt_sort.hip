@@ -83,18 +83,23 @@ __global__ void k_chunk_bbox(const double *__restrict__ xyz, const uint64_t *__r
     if (threadIdx.x < 6) partial[6 * blockIdx.x + threadIdx.x] = sh[threadIdx.x][0];
 }
 
-// one thread per cloud: its box from its chunks; the grid origin and the cubic scale
+// one wavefront per cloud: its box from its chunks; the grid origin and the cubic scale
 // 2^m / (largest extent)
-__global__ void k_cloud_box(const double *__restrict__ partial, const uint32_t *__restrict__ cloud_ch,
-                            uint32_t nclouds, Cloud *__restrict__ clouds) {
-    const uint32_t c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= nclouds) return;
+__global__ __launch_bounds__(64) void k_cloud_box(const double *__restrict__ partial,
+                                                  const uint32_t *__restrict__ cloud_ch, Cloud *__restrict__ clouds) {
+    const uint32_t c = blockIdx.x;
     double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
-    for (uint32_t j = cloud_ch[c]; j < cloud_ch[c + 1]; ++j)
+    for (uint32_t j = cloud_ch[c] + threadIdx.x; j < cloud_ch[c + 1]; j += 64)
         for (int k = 0; k < 3; ++k) {
             lo[k] = fmin(lo[k], partial[6 * j + k]);
             hi[k] = fmax(hi[k], partial[6 * j + 3 + k]);
         }
+    for (int o = 32; o > 0; o >>= 1)
+        for (int k = 0; k < 3; ++k) {
+            lo[k] = fmin(lo[k], __shfl_xor(lo[k], o, 64));
+            hi[k] = fmax(hi[k], __shfl_xor(hi[k], o, 64));
+        }
+    if (threadIdx.x != 0) return;
     double ext = 0.0;
     for (int k = 0; k < 3; ++k) {
         const double e = hi[k] - lo[k];
@@ -111,7 +116,7 @@ hipError_t launch_cloud_bbox(const double *xyz, const uint64_t *ch_start, const 
                              uint32_t nchunks, double *partial, const uint32_t *cloud_ch, uint32_t nclouds,
                              Cloud *clouds, uint32_t *err, hipStream_t s) {
     if (nchunks) k_chunk_bbox<<<nchunks, 256, 0, s>>>(xyz, ch_start, ch_end, partial, err);
-    k_cloud_box<<<(nclouds + 255) / 256, 256, 0, s>>>(partial, cloud_ch, nclouds, clouds);
+    if (nclouds) k_cloud_box<<<nclouds, 64, 0, s>>>(partial, cloud_ch, clouds);
     return hipGetLastError();
 }
 
