@@ -922,20 +922,42 @@ int run_rounds(dt_ctx *c, const Levels &lv, const uint32_t *d_start, const uint3
     uint32_t fly_cand = 0;   // its candidates (exact)
     double loss = 0.5;       // share of candidates lost by the last completed round
     uint32_t won_seen = c->hctr->won;
+    // Several clouds: the points of a level come from the clouds that reach it, and the cloud with
+    // most of them sets how many fit a round.  Where that cloud has V vertices when the level
+    // begins and p points in it, and the level has P points in all, a round of f P (V / p + x)
+    // candidates, x of the level done, holds the share f of that cloud's vertices (one cloud:
+    // V + p x, the mesh).  Sized from all clouds' vertices, rounds of the late levels crowded the
+    // few large clouds: 64 clouds of 1000 to 2e5 points, 65 % of the attempts conflicted.
+    std::vector<double> lvl_share;  // V / p of each level
+    if (c->call_clouds > 1 && !lv.halves) {
+        for (int k = 0; k < lv.L; ++k) {
+            uint64_t most = 0;
+            for (uint32_t q = 0; q < c->call_clouds; ++q) most = std::max(most, c->h_off[q + 1] - c->h_off[q]);
+            const uint64_t before = k ? brio_cum(most)[std::min<size_t>(k - 1, brio_cum(most).size() - 1)] : 0;
+            const uint64_t upto = brio_cum(most)[std::min<size_t>(k, brio_cum(most).size() - 1)];
+            lvl_share.push_back(upto > before ? (double)before / (double)(upto - before) : 0.0);
+        }
+    }
     auto target_size = [&]() {
         double f = frac;
+        double vertices = (double)c->mesh_vertices;
+        if (!lvl_share.empty() && next_rank < lv.total_ranks) {
+            int k = 0;
+            while (k + 1 < lv.L && lv.rank_base[k + 1] <= next_rank) ++k;
+            const double x = (double)(next_rank - lv.rank_base[k]) / (double)(lv.rank_base[k + 1] - lv.rank_base[k]);
+            if (k) vertices = std::min(vertices, (double)lv.size[k] * (lvl_share[k] + x));
+        }
         if (lv.halves && next_rank < lv.total_ranks) {
             // the points predicted costly conflict more: fewer of them per round
             int k = 0;
             while (k + 1 < lv.L && lv.rank_base[k + 1] <= next_rank) ++k;
             if (k & 1) f *= c->costly_scale;
         }
-        uint64_t t = (uint64_t)std::llround(f * (double)c->mesh_vertices);
+        uint64_t t = (uint64_t)std::llround(f * vertices);
         // automatic fraction: short rounds, which last as long as their slowest insertion
         // whatever their size, take a larger share (up to SMALL_ROUND candidates)
         if (c->frac_auto && t < SMALL_ROUND)
-            t = std::min<uint64_t>(SMALL_ROUND, (uint64_t)std::llround(f * SHORT_ROUND_FRACTION_SCALE *
-                                                                     (double)c->mesh_vertices));
+            t = std::min<uint64_t>(SMALL_ROUND, (uint64_t)std::llround(f * SHORT_ROUND_FRACTION_SCALE * vertices));
         if (c->opt.round_size) return std::min<uint64_t>(c->opt.round_size, rmax);
         return std::min<uint64_t>(std::max<uint64_t>(t, ROUND_MIN), rmax);
     };
