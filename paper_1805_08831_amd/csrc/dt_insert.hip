@@ -482,6 +482,7 @@ __global__ __launch_bounds__(256) void k_cavity_g(RoundArgs a) {
     const uint32_t stride = a.stride;
     PredStats st;
     unsigned steps = 0, attempt = 0;
+    bool deferred = false;
     // one candidate per group; the deferred pass strides over its short list
     for (uint32_t j = blockIdx.x * GPB + gi; j < ncand; j += DEFER ? gridDim.x * GPB : ncand) {
         const uint32_t i = DEFER ? a.defer[j] : j;
@@ -768,10 +769,11 @@ __global__ __launch_bounds__(256) void k_cavity_g(RoundArgs a) {
             a.status[i] = status;
             a.cnt[i] = ncav;
             a.cnt[stride + i] = nbnd;
-            if (!FULL && status == ST_FULL) a.defer[atomicAdd(a.ndefer_ptr, 1u)] = i;
+            if (!FULL && status == ST_FULL) deferred = true;
             else attempt++;  // a deferred attempt is counted by the FULL kernel
         }
     }
+    if (!FULL) add_count(a.stat, STAT_DEFERRED, deferred);
     if (gl != 0) steps = 0;
     add_stat(a.stat, STAT_ATTEMPTS, attempt);
     add_stat(a.stat, STAT_WALK, steps);
@@ -1083,6 +1085,8 @@ __device__ __forceinline__ void roll_counters(const RoundArgs &a, bool carry, co
                 ctr->won = (uint32_t)x;
             } else if (id == STAT_WALK_CAPS) {
                 ctr->walk_caps = (uint32_t)x;
+            } else if (id == STAT_DEFERRED) {
+                ctr->deferred = (uint32_t)x;
             } else if (id == STAT_OVERFLOWS) {
                 s_ovf = (uint32_t)x - ctr->overflows;
                 ctr->overflows = (uint32_t)x;
@@ -1110,7 +1114,6 @@ __device__ __forceinline__ void roll_counters(const RoundArgs &a, bool carry, co
         const uint32_t left = take < fln ? fln - take : 0u;
         const uint32_t nxt = min(freed, a.flcap), keep = min(left, a.flcap - nxt);
         ctr->dropped += (freed - nxt) + (left - keep);
-        ctr->deferred += ctr->ndefer;
         ctr->ndefer = 0;
         ctr->fl_n = nxt + keep;
         ctr->fl_take = 0;
@@ -1239,6 +1242,17 @@ __device__ __forceinline__ void select_attempts(const RoundArgs &a, uint32_t i) 
     add_count(a.stat, STAT_WALK_CAPS, any && status == ST_WALK);
 }
 
+// The attempts the filter pass left undecided, listed for the exact pass.  Listed by the filter
+// pass itself, each with an atomic on the one counter (55 ns one after the other), the 2,000 of
+// an average round on mixed points held it up by half its time.
+__global__ __launch_bounds__(FILL_BLOCK) void k_defer(RoundArgs a) {
+    __shared__ uint32_t s_tmp[FILL_BLOCK / 64 + 1];
+    const uint32_t i = blockIdx.x * FILL_BLOCK + threadIdx.x;
+    const bool full = i < *a.ncand_ptr && a.status[i] == ST_FULL;
+    const uint32_t at = block_reserve<FILL_BLOCK / 64, uint32_t>(full ? 1u : 0u, a.ndefer_ptr, s_tmp);
+    if (full) a.defer[at] = i;
+}
+
 template <class K>
 __global__ __launch_bounds__(FILL_BLOCK) void k_select(RoundArgs a) {
     select_attempts<K>(a, blockIdx.x * FILL_BLOCK + threadIdx.x);
@@ -1283,23 +1297,29 @@ __global__ __launch_bounds__(ROLL_BLOCK) void k_select_roll(RoundArgs a, uint32_
 // the cavity boundary is a closed surface, so each edge lies on exactly two boundary
 // facets, and the two new tetrahedra on them are the siblings.  They are paired through a
 // hash table of edges in LDS, and each record is stored once it is complete (one row of
-// vertices, one of neighbours).  Balls too large for the table pair siblings by pivoting
-// around the edge through copies of the cavity tetrahedra instead.
-constexpr uint32_t HT = 128;             // edge table entries per candidate
-constexpr uint32_t HT_MAX_FACETS = 64;   // balls up to this size use the table (load <= 3/4)
+// vertices, one of neighbours).  Balls too large for the table (64 facets with 16 lanes, 256
+// with 64, 2048 with the whole block) pair siblings by pivoting around the edge through copies
+// of the cavity tetrahedra in memory instead, a chain of dependent loads for every edge.  In
+// rounds for large cavities (170 tetrahedra on average on mixed points) one wavefront per ball
+// and pivots beyond 64 facets took 146 us a launch.
+// edge table entries per candidate; balls of up to half as many facets use it (load <= 3/4)
+__host__ __device__ constexpr int ball_table_bits(int GL) { return GL == 16 ? 7 : (GL == 64 ? 9 : 12); }
 constexpr unsigned long long HT_EMPTY = ~0ull;
 // threads per block of the ball kernel: the slot reservation is one atomic per block on one
 // counter, so larger blocks contend less (at the cost of LDS occupancy)
 constexpr int BALL_BLOCK = 256;
 
-// orders the memory accesses of one group (all in one wave) across phases
+// orders the memory accesses of one group (part of one wave, or the whole block) across phases
+template <bool BLOCK>
 __device__ __forceinline__ void group_fence() {
     __threadfence_block();
-    __builtin_amdgcn_wave_barrier();
+    if (BLOCK) __syncthreads();
+    else __builtin_amdgcn_wave_barrier();
 }
 
+template <int BITS>
 __device__ __forceinline__ uint32_t edge_hash(unsigned long long key) {
-    return (uint32_t)((key * 0x9E3779B97F4A7C15ull) >> 57);  // 7 bits: HT = 128
+    return (uint32_t)((key * 0x9E3779B97F4A7C15ull) >> (64 - BITS));
 }
 
 // the edge of the boundary facet opposite vertex f that lies in facet q of the new tetrahedron
@@ -1319,7 +1339,10 @@ template <class K, int GL, int BS>
 __global__ __launch_bounds__(BS) void k_ball(RoundArgs a) {
     using code = typename K::code;
     constexpr code LOC_BOUNDARY = (code)1 << (8 * sizeof(code) - 1);
+    constexpr bool BLOCK = GL == BS;  // the whole block builds one ball
     constexpr uint32_t GPB = BS / GL;
+    constexpr int BITS = ball_table_bits(GL);
+    constexpr uint32_t HT = 1u << BITS, HT_MAX_FACETS = HT / 2;
     // edge table: key = the edge's two vertices; value = (boundary facet b << 2 | facet q of
     // b's new tetrahedron) for the two new tetrahedra on the edge; the slot of b's new
     // tetrahedron is in s_slot[b] (b < HT_MAX_FACETS on this path)
@@ -1327,11 +1350,8 @@ __global__ __launch_bounds__(BS) void k_ball(RoundArgs a) {
     __shared__ uint16_t s_val[GPB][HT][2];
     __shared__ uint32_t s_slot[GPB][HT_MAX_FACETS];
     typename K::Rec *const T = static_cast<typename K::Rec *>(a.T);
-    const uint32_t lane = threadIdx.x & 63u;
     const uint32_t gl = threadIdx.x % GL;
     const uint32_t gi = threadIdx.x / GL;
-    const uint32_t gbase = lane & ~(uint32_t)(GL - 1);
-    const unsigned long long gmask = GL == 64 ? ~0ull : (((1ull << (GL & 63)) - 1ull) << gbase);
     const uint32_t wi = blockIdx.x * GPB + gi;
     if (wi >= a.ctr->ball_wins) return;  // whole groups; no barrier below
     const unsigned long long tb0 = a.clk ? (unsigned long long)wall_clock64() : 0ull;
@@ -1353,7 +1373,8 @@ __global__ __launch_bounds__(BS) void k_ball(RoundArgs a) {
         // gl, gl + GL, ... from registers.  Everything read from the cavity is read before the
         // first store into it.
         constexpr int NB = (int)HT_MAX_FACETS / GL;
-        uint32_t slot[NB], at[NB];
+        uint32_t slot[NB];
+        unsigned long long at[NB];  // table entries of the facets' edges, 16 bits each
         int fq[NB];
         code oc[NB];
         uint4 w[NB];
@@ -1377,7 +1398,7 @@ __global__ __launch_bounds__(BS) void k_ball(RoundArgs a) {
             s_key[gi][h] = HT_EMPTY;
             s_val[gi][h][0] = s_val[gi][h][1] = 0xFFFFu;
         }
-        group_fence();
+        group_fence<BLOCK>();
         if (a.clk) tb2 = (unsigned long long)wall_clock64();
         // edges of the boundary facets into the table; facet q of the new tetrahedron holds p
         // and the edge of the boundary facet without vertex q
@@ -1398,13 +1419,13 @@ __global__ __launch_bounds__(BS) void k_ball(RoundArgs a) {
                 for (int q = 0; q < 4; ++q) {
                     if (q == f) continue;
                     const unsigned long long key = facet_edge(wv, q, f);
-                    uint32_t h = edge_hash(key);
+                    uint32_t h = edge_hash<BITS>(key);
                     bool placed = false;
                     for (uint32_t probe = 0; probe < HT && !placed; ++probe) {
                         const unsigned long long old = atomicCAS(&s_key[gi][h], HT_EMPTY, key);
                         if (old == HT_EMPTY || old == key) {
                             s_val[gi][h][old == HT_EMPTY ? 0 : 1] = (uint16_t)((b << 2) | (uint32_t)q);
-                            at[k] |= h << (8 * q);
+                            at[k] |= (unsigned long long)h << (16 * q);
                             placed = true;
                         } else {
                             h = (h + 1) & (HT - 1);
@@ -1414,7 +1435,8 @@ __global__ __launch_bounds__(BS) void k_ball(RoundArgs a) {
                 }
             }
         }
-        lane_fence<false>();
+        if (BLOCK) __syncthreads();
+        else lane_fence<false>();
         // the siblings across the three facets through p; then the record, one aligned row of
         // vertices and one of neighbours
 #pragma unroll
@@ -1428,7 +1450,7 @@ __global__ __launch_bounds__(BS) void k_ball(RoundArgs a) {
                 for (int q = 0; q < 4; ++q) {
                     code c = oc[k];  // facet opposite p: the outer tetrahedron
                     if (q != f) {
-                        const uint32_t h = (at[k] >> (8 * q)) & 255u;
+                        const uint32_t h = (uint32_t)(at[k] >> (16 * q)) & 0xFFFFu;
                         const uint32_t mine = (b << 2) | (uint32_t)q;
                         const uint32_t v0 = s_val[gi][h][0], v1 = s_val[gi][h][1];
                         uint32_t res = v0 == mine ? v1 : v0;
@@ -1466,7 +1488,7 @@ __global__ __launch_bounds__(BS) void k_ball(RoundArgs a) {
             sn[k] = T[c].n;
             T[c].spare[0] = k;
         }
-        group_fence();
+        group_fence<BLOCK>();
         if (a.clk) tb2 = (unsigned long long)wall_clock64();
         // facets between two cavity tetrahedra -> local codes
         for (uint32_t task = gl; task < 4 * nc; task += GL) {
@@ -1477,7 +1499,7 @@ __global__ __launch_bounds__(BS) void k_ball(RoundArgs a) {
             if (T[nt].claim == claim_stamp(a, i))  // only this winner's cavity tetrahedra hold S
                 reinterpret_cast<code *>(&sn[k])[f] = make_code<K>((uint32_t)T[nt].spare[0], code_facet(cd));
         }
-        group_fence();
+        group_fence<BLOCK>();
         // one new tetrahedron per boundary facet (k, f): k with v_f replaced by p
         for (uint32_t b = gl; b < nb; b += GL) {
             uint32_t slot;
@@ -1508,7 +1530,7 @@ __global__ __launch_bounds__(BS) void k_ball(RoundArgs a) {
                 if (wv[q] != GHOST && (q != f || b == 0)) a.vtet[wv[q]] = slot;
             reinterpret_cast<code *>(&sn[kb])[f] = LOC_BOUNDARY | (code)b;
         }
-        group_fence();
+        group_fence<BLOCK>();
         // the three siblings of each new tetrahedron
         for (uint32_t task = gl; task < 3 * nb; task += GL) {
             const uint32_t b = task / 3, qi = task - 3 * b;
@@ -1604,19 +1626,21 @@ static hipError_t launch_round_k(const RoundArgs &a, uint32_t max_cand, uint32_t
         k_cavity_g<K, 64, BIG_CAPC, BIG_HM, false, true, false><<<(max_cand + 3) / 4, 256, 0, s>>>(a);
     } else if (lanes == 4) {
         k_cavity_g<K, 4, LCAPC, LHM, false, false, false><<<(max_cand + 63) / 64, 256, 0, s>>>(a);
-        if (exact) k_cavity_g<K, EXACT_LANES, LCAPC, LHM, false, true, true><<<dgrid, 256, 0, s>>>(a);
     } else if (lanes == 8) {
         k_cavity_g<K, 8, LCAPC, LHM, false, false, false><<<(max_cand + 31) / 32, 256, 0, s>>>(a);
-        if (exact) k_cavity_g<K, EXACT_LANES, LCAPC, LHM, false, true, true><<<dgrid, 256, 0, s>>>(a);
     } else if (lanes == 32) {
         k_cavity_g<K, 32, LCAPC, LHM, false, false, false><<<(max_cand + 7) / 8, 256, 0, s>>>(a);
-        if (exact) k_cavity_g<K, EXACT_LANES, LCAPC, LHM, false, true, true><<<dgrid, 256, 0, s>>>(a);
     } else if (lanes == 64) {
         k_cavity_g<K, 64, LCAPC, LHM, false, false, false><<<(max_cand + 3) / 4, 256, 0, s>>>(a);
-        if (exact) k_cavity_g<K, EXACT_LANES, LCAPC, LHM, false, true, true><<<dgrid, 256, 0, s>>>(a);
     } else {
         k_cavity_g<K, 16, LCAPC, LHM, false, false, false><<<(max_cand + 15) / 16, 256, 0, s>>>(a);
-        if (exact) k_cavity_g<K, EXACT_LANES, LCAPC, LHM, false, true, true><<<dgrid, 256, 0, s>>>(a);
+    }
+    if (exact && a.capC <= LCAPC) {
+        k_defer<<<(max_cand + FILL_BLOCK - 1) / FILL_BLOCK, FILL_BLOCK, 0, s>>>(a);
+        if (lanes == 64)
+            k_cavity_g<K, 64, LCAPC, LHM, false, true, true><<<std::min<uint32_t>((max_cand + 3) / 4, DEFER_BLOCKS), 256, 0, s>>>(a);
+        else
+            k_cavity_g<K, EXACT_LANES, LCAPC, LHM, false, true, true><<<dgrid, 256, 0, s>>>(a);
     }
     if (ev) hipEventRecord(ev[1], s);
     const bool apart = end.free_slots > ROLL_CARRY;
@@ -1627,9 +1651,11 @@ static hipError_t launch_round_k(const RoundArgs &a, uint32_t max_cand, uint32_t
         if (apart) k_freelist_carry<<<256, 256, 0, s>>>(a);
         k_roll<<<1, ROLL_BLOCK, 0, s>>>(a, apart ? 0u : 1u, end);
     }
-    // rounds for large cavities build large balls (their siblings found by pivoting), and
-    // short rounds wait on their slowest candidate: a wavefront per candidate
-    if (a.capC > LCAPC || lanes == 64)
+    // a block per ball in rounds for large cavities, a wavefront in short rounds, which wait on
+    // their slowest attempt, 16 lanes in the rest
+    if (a.capC > LCAPC)
+        k_ball<K, BALL_BLOCK, BALL_BLOCK><<<max_cand, BALL_BLOCK, 0, s>>>(a);
+    else if (lanes == 64)
         k_ball<K, 64, BALL_BLOCK><<<(max_cand + BALL_BLOCK / 64 - 1) / (BALL_BLOCK / 64), BALL_BLOCK, 0, s>>>(a);
     else
         k_ball<K, 16, BALL_BLOCK><<<(max_cand + BALL_BLOCK / 16 - 1) / (BALL_BLOCK / 16), BALL_BLOCK, 0, s>>>(a);
@@ -1709,11 +1735,12 @@ hipError_t launch_round_graph(RoundGraph *graphs, const FillPlan &plan, const Fi
     const uint32_t gpb = 256 / L;
     set(0, (void *)k_fill, (fill_count + FILL_BLOCK - 1) / FILL_BLOCK, FILL_BLOCK, fill_args);
     set(1, k_cav, (max_cand + gpb - 1) / gpb, 256, round_args);
-    set(2, k_exact, std::min<uint32_t>((max_cand + 256 / EXACT_LANES - 1) / (256 / EXACT_LANES), DEFER_BLOCKS), 256, round_args);
-    set(3, wide ? (void *)k_select<Wide> : (void *)k_select<Narrow>, (max_cand + FILL_BLOCK - 1) / FILL_BLOCK,
+    set(2, (void *)k_defer, (max_cand + FILL_BLOCK - 1) / FILL_BLOCK, FILL_BLOCK, round_args);
+    set(3, k_exact, std::min<uint32_t>((max_cand + 256 / EXACT_LANES - 1) / (256 / EXACT_LANES), DEFER_BLOCKS), 256, round_args);
+    set(4, wide ? (void *)k_select<Wide> : (void *)k_select<Narrow>, (max_cand + FILL_BLOCK - 1) / FILL_BLOCK,
         FILL_BLOCK, round_args);
-    set(5, k_b, (max_cand + BALL_BLOCK / gl_ball - 1) / (BALL_BLOCK / gl_ball), BALL_BLOCK, round_args);
-    set(4, (void *)k_roll, 1, ROLL_BLOCK, roll_args);
+    set(6, k_b, (max_cand + BALL_BLOCK / gl_ball - 1) / (BALL_BLOCK / gl_ball), BALL_BLOCK, round_args);
+    set(5, (void *)k_roll, 1, ROLL_BLOCK, roll_args);
     hipError_t e;
     if (!g.exec) {
         if ((e = hipGraphCreate(&g.graph, 0)) != hipSuccess) return e;

@@ -91,7 +91,7 @@ enum : uint32_t {
 // waves do not serialize on one address; k_roll sums them into Ctr.
 enum : int {
     STAT_ATTEMPTS = 0, STAT_WALK, STAT_ORIENT, STAT_ORIENT_EXACT, STAT_INSPHERE, STAT_INSPHERE_EXACT,
-    STAT_PERTURBED, STAT_CAV_TETS, STAT_BND_FACETS, STAT_WON, STAT_OVERFLOWS, STAT_WALK_CAPS, NSTAT
+    STAT_PERTURBED, STAT_CAV_TETS, STAT_BND_FACETS, STAT_WON, STAT_OVERFLOWS, STAT_WALK_CAPS, STAT_DEFERRED, NSTAT
 };
 constexpr int STAT_SPREAD = 64;
 constexpr int STAT_PAD = 16;  // u64 words per counter (128 bytes)
@@ -324,7 +324,7 @@ struct FillArgs {
     const uint32_t *vtet;
     uint32_t *cand_pt, *cand_rank, *ncand;
 };
-constexpr int ROUND_GRAPH_NODES = 6;
+constexpr int ROUND_GRAPH_NODES = 7;
 struct RoundGraph {
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
