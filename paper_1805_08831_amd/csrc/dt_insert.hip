@@ -643,7 +643,7 @@ __global__ __launch_bounds__(256) void k_cavity_g(RoundArgs a) {
                 const uint32_t c = code_slot(cd);
                 const int pf = slot == 0 ? -1 : code_facet(cd);
                 const bool act = lv && f != pf;
-                uint4 cv = make_uint4(0u, 0u, 0u, 0u), uw = cv;
+                uint4 cv = make_uint4(0u, 0u, 0u, 0u);
                 typename K::code4 cn{};
                 if (lv) {
                     cv = T[c].v;
@@ -660,29 +660,33 @@ __global__ __launch_bounds__(256) void k_cavity_g(RoundArgs a) {
                 const uint32_t u = code_slot(ncode);
                 const int kind = act ? mem_find<GLOBAL, SPLIT>(mem, kinds, hms, u) : -1;  // 0: in this cavity, 1: outside it
                 const bool need = act && kind < 0;
-                if (need) uw = T[u].v;
+                uint32_t apex = 0;  // vertex of u across facet f
+                if (need) apex = reinterpret_cast<const uint32_t *>(&T[u].v)[code_facet(ncode)];
                 bool inside = false, undecided = false;
                 if (need) {
                     const bool cghost = cv.w == GHOST;
-                    const uint32_t apex = comp(uw, code_facet(ncode));
                     if (!cghost && apex != GHOST) {
-                        // u = facet f of c + apex; c with vertex f replaced by the apex and
-                        // two entries swapped is positively oriented
-                        const uint32_t cid[4] = {cv.x, cv.y, cv.z, cv.w};
+                        // u = facet f of c + apex: c with vertex f replaced by the apex is
+                        // negatively oriented, which swaps the filter's signs; the exact
+                        // predicates get it with two entries swapped
                         uint32_t rid[4];
 #pragma unroll
-                        for (int m = 0; m < 4; ++m) rid[m] = m == f ? apex : cid[m];
-                        const int sa = (f + 1) & 3, sb = (f + 2) & 3;
-                        uint32_t r2[4];
-#pragma unroll
-                        for (int m = 0; m < 4; ++m) r2[m] = m == sa ? rid[sb] : (m == sb ? rid[sa] : rid[m]);
+                        for (int m = 0; m < 4; ++m) rid[m] = m == f ? apex : comp(cv, m);
                         int si;
                         if (!FULL && a.subd) {
-                            // cached sub-determinants of u (its stored vertex order is positive too,
-                            // an even permutation of r2, so the sign is the same)
+                            // cached sub-determinants of u (its stored vertex order is positive)
                             st.insphere++;
-                            si = insphere_cached(static_cast<const SubD *>(a.subd)[u], vpos(a.V, uw.x), P);
+                            si = insphere_cached(static_cast<const SubD *>(a.subd)[u], vpos(a.V, T[u].v.x), P);
+                        } else if (!FULL) {
+                            st.insphere++;
+                            const int neg = insphere_filter(vpos(a.V, rid[0]), vpos(a.V, rid[1]), vpos(a.V, rid[2]),
+                                                            vpos(a.V, rid[3]), P);
+                            si = neg == 0 || neg == 2 ? UNDECIDED : -neg;
                         } else {
+                            const int sa = (f + 1) & 3, sb = (f + 2) & 3;
+                            uint32_t r2[4];
+#pragma unroll
+                            for (int m = 0; m < 4; ++m) r2[m] = m == sa ? rid[sb] : (m == sb ? rid[sa] : rid[m]);
                             si = cav_insphere<FULL>(vpos(a.V, r2[0]), vpos(a.V, r2[1]), vpos(a.V, r2[2]),
                                                     vpos(a.V, r2[3]), P,
                                                     [&](int kk) { return kk < 4 ? a.V[r2[kk]].idx : pv.idx; }, st);
