@@ -167,6 +167,7 @@ struct dt_ctx {
     // output scratch
     DevBuf<unsigned long long> obits;  // export: live bit set, one word per 64 slots
     DevBuf<uint32_t> owcnt, opre, otets, ovid;
+    DevBuf<uint4> owords;              // the bit set packed with its scan
     DevBuf<int64_t> onbrs;
 
     hipEvent_t ev[3][3] = {};   // per snapshot slot: kernel timing events of its round
@@ -1513,7 +1514,8 @@ int dt_get_tets(dt_ctx *c, uint32_t *tets, int64_t *nbrs, uint64_t *num_tets) {
         return fail(c, DT_E_ARG, "output buffers hold %llu tetrahedra, %u needed", (unsigned long long)*num_tets, T);
     }
     *num_tets = T;
-    if ((rc = ensure(c, c->ovid, std::max<uint64_t>(c->nv, 1)))) return rc;
+    if ((rc = ensure(c, c->ovid, std::max<uint64_t>(c->nv, 1))) || (rc = ensure(c, c->owords, nw))) return rc;
+    HIPCHK(launch_live_words(c->obits.p, c->opre.p, (uint32_t)nw, c->owords.p, c->stream));
     HIPCHK(launch_out_vid(c->V.p, (uint32_t)c->nv, c->ovid.p, c->stream));
     // The export kernel stores 16-byte vectors: host buffers and device buffers that are not
     // 16-byte aligned are filled through staging buffers, a slot range at a time (chunk
@@ -1540,7 +1542,7 @@ int dt_get_tets(dt_ctx *c, uint32_t *tets, int64_t *nbrs, uint64_t *num_tets) {
         const uint32_t o0 = obase[k], o1 = obase[k + 1];
         uint32_t *ot = tets ? (dev_t ? tets + 4 * (size_t)o0 : c->otets.p) : nullptr;
         int64_t *on = nbrs ? (dev_n ? nbrs + 4 * (size_t)o0 : c->onbrs.p) : nullptr;
-        HIPCHK(launch_output(c->T, c->wide, c->ovid.p, c->obits.p, c->opre.p, t0, t1, o0, ot, on, c->stream));
+        HIPCHK(launch_output(c->T, c->wide, c->ovid.p, c->owords.p, t0, t1, o0, ot, on, c->stream));
         if (tets && !dev_t && o1 > o0)
             HIPCHK(hipMemcpyAsync(tets + 4 * (size_t)o0, ot, 4 * (size_t)(o1 - o0) * sizeof(uint32_t),
                                   hipMemcpyDefault, c->stream));
@@ -1953,7 +1955,7 @@ int dt_destroy(dt_ctx *c) {
     f(c->okeys.p); f(c->osorted.p); f(c->omap2.p); f(c->dbgV.p); f(c->dbg_cloud.p);
     f(c->lev.p); f(c->wbucket.p); f(c->log_att.p); f(c->feat.p); f(c->ypred.p);
     f(c->w32.p); f(c->m1.p); f(c->m2.p); f(c->grad.p); f(c->loss.p); f(c->wbf.p);
-    f(c->obits.p); f(c->owcnt.p); f(c->opre.p); f(c->otets.p); f(c->onbrs.p); f(c->ovid.p);
+    f(c->obits.p); f(c->owcnt.p); f(c->opre.p); f(c->owords.p); f(c->otets.p); f(c->onbrs.p); f(c->ovid.p);
     f(c->rf_cc.p); f(c->rf_cc2.p); f(c->rf_ccr.p); f(c->rf_pts.p); f(c->rf_partial.p);
     f(c->rf_q.p); f(c->rf_q2.p); f(c->rf_facets.p); f(c->rf_moore.p); f(c->rf_k0.p); f(c->rf_k1.p);
     f(c->rf_v0.p); f(c->rf_v1.p); f(c->rf_ctr.p); f(c->rf_flags.p); f(c->rf_pos.p);

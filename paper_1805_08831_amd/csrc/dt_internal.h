@@ -337,14 +337,16 @@ void destroy_round_graphs(RoundGraph *graphs);
 hipError_t launch_reset_claims(void *T, bool wide, uint32_t tcap, hipStream_t s);
 // copies `count` Tet records into TetW records
 hipError_t launch_widen(const void *src, void *dst, uint32_t count, hipStream_t s);
-// export: live bit set (one word per 64 slots) with per-word counts, input index per vertex
-// record, and the output rows of live slots [t0, t1) at out_index - obase
+// export: live bit set (one word per 64 slots) with per-word counts, both packed with the scan of
+// the counts (words[w] = bits, tetrahedra before), input index per vertex record, and the output
+// rows of live slots [t0, t1) at out_index - obase
 hipError_t launch_live_bits(const void *T, bool wide, uint32_t count, unsigned long long *bits, uint32_t *wcnt,
                             hipStream_t s);
+hipError_t launch_live_words(const unsigned long long *bits, const uint32_t *pre, uint32_t nwords, uint4 *words,
+                             hipStream_t s);
 hipError_t launch_out_vid(const Vert *V, uint32_t nv, uint32_t *vid, hipStream_t s);
-hipError_t launch_output(const void *T, bool wide, const uint32_t *vid, const unsigned long long *bits,
-                         const uint32_t *pre, uint32_t t0, uint32_t t1, uint32_t obase, uint32_t *tets, int64_t *nbrs,
-                         hipStream_t s);
+hipError_t launch_output(const void *T, bool wide, const uint32_t *vid, const uint4 *words, uint32_t t0, uint32_t t1,
+                         uint32_t obase, uint32_t *tets, int64_t *nbrs, hipStream_t s);
 // grouping of the live finite tetrahedra by cloud (see dt_get_tets_batch)
 hipError_t launch_tet_cloud(const void *T, bool wide, const Vert *V, uint32_t count, uint32_t nclouds,
                             unsigned long long *keys, uint32_t *vals, hipStream_t s);

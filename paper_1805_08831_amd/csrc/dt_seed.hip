@@ -320,7 +320,7 @@ __global__ __launch_bounds__(SEED_THREADS) void k_seed(const Vert *__restrict__ 
                         // One orient3d and one insphere for all cases (lanes of different
                         // cases would run one after the other):
                         //   c finite, u finite: insphere of facet f of c and the apex across
-                        //     it, two entries swapped (positive)
+                        //     it (negatively oriented: the sign turned)
                         //   c finite, u ghost: inside iff P is beyond facet f
                         //   c ghost, u ghost: inside iff P is beyond u's finite facet
                         //   c ghost, u finite: insphere of u
@@ -328,17 +328,11 @@ __global__ __launch_bounds__(SEED_THREADS) void k_seed(const Vert *__restrict__ 
                         const ushort4 uv = s.v[u];
                         const uint32_t apex = at4(uv, (int)(ncode & 3u));
                         const bool plane = cghost ? uv.w == LGHOST : apex == LGHOST;
+                        const bool swapped = !cghost && !plane;  // negatively oriented as it stands
                         uint32_t q[4];
-                        const int sa = (f + 1) & 3, sb = (f + 2) & 3;
 #pragma unroll
                         for (int k = 0; k < 4; ++k)
-                            q[k] = cghost || plane ? at4(cghost ? uv : cv, k)
-                                                   : at4(cv, k == sa ? sb : (k == sb ? sa : k));
-                        if (!cghost && !plane) {
-#pragma unroll
-                            for (int k = 0; k < 4; ++k)
-                                if (k == f) q[k] = apex;
-                        }
+                            q[k] = cghost ? at4(uv, k) : (k == f && !plane ? apex : at4(cv, k));
                         int side = 0;
                         if (plane) {
                             P3 r[4];
@@ -347,7 +341,10 @@ __global__ __launch_bounds__(SEED_THREADS) void k_seed(const Vert *__restrict__ 
                             const int o = seed_orient(r[0], r[1], r[2], r[3], st);
                             side = o == UNSURE || !cghost ? o : -o;
                         }
-                        if (!plane) side = seed_insphere(s, q, P, st);
+                        if (!plane) {
+                            side = seed_insphere(s, q, P, st);
+                            if (swapped && side != UNSURE) side = -side;
+                        }
                         inside = side < 0;
                         unsure = side == UNSURE;
                         const uint32_t old = unsure ? ~0u : atomicMin(&s.claim[u], inside ? S : S + 1);
