@@ -1056,90 +1056,103 @@ __device__ __forceinline__ U fresh(const U *p) {
 }
 
 // the unused part of this round's free list goes behind the slots freed this round (as far as
-// the list holds them)
-__device__ __forceinline__ void carry_free(const RoundArgs &a, uint32_t from, uint32_t step) {
-    const uint32_t fln = a.ctr->fl_n, take = fresh(&a.ctr->fl_take), nxt = min(fresh(&a.ctr->fl_next), a.flcap);
+// the list holds them); ctr: the counters or a copy of them
+__device__ __forceinline__ void carry_free(const RoundArgs &a, const Ctr *ctr, uint32_t from, uint32_t step) {
+    const uint32_t fln = ctr->fl_n, take = ctr->fl_take, nxt = min(ctr->fl_next, a.flcap);
     if (take >= fln) return;
     const uint32_t left = min(fln - take, a.flcap - nxt);
     for (uint32_t k = from; k < left; k += step) a.fl_next[nxt + k] = a.fl_cur[take + k];
 }
 
 __global__ void k_freelist_carry(RoundArgs a) {
-    carry_free(a, blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x);
+    carry_free(a, a.ctr, blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x);
 }
 
-// Round end, one block: the free list's rest carried, the statistics summed (one wavefront per
-// statistic), the pool's counters advanced (the ball kernel, which follows, finds what it needs
-// of the old ones beside them).  With end.snap (pinned host memory), the counters are then
-// written there and `seq` (host memory too) is set to `tag` after them with a release at system
-// scope: the host waits for that value instead of for a copy and an event.
+// Round end, one block: the statistics summed (one wavefront per statistic) while one wavefront
+// copies the counters to LDS, the pool's counters advanced there and written back (the ball
+// kernel, which follows, finds what it needs of the old ones beside them), the free list's rest
+// carried.  With end.snap (pinned host memory), the copy is then written there and `seq` (host
+// memory too) is set to `tag` after it with a release at system scope: the host waits for that
+// value instead of for a copy and an event.
 constexpr int ROLL_BLOCK = 1024;
-static_assert(NSTAT * 64 <= ROLL_BLOCK && STAT_SPREAD == 64, "one wavefront sums one statistic");
+constexpr uint32_t CTR_WORDS = sizeof(Ctr) / sizeof(uint32_t);
+typedef uint32_t __attribute__((may_alias)) word_t;
+static_assert(NSTAT * 64 + 64 <= ROLL_BLOCK && STAT_SPREAD == 64, "one wavefront sums one statistic, another copies");
+static_assert(sizeof(Ctr) % sizeof(uint32_t) == 0 && CTR_WORDS <= 64, "one wavefront copies the counters in words");
 
 __device__ __forceinline__ void roll_counters(const RoundArgs &a, bool carry, const RoundEnd &end) {
+    __shared__ Ctr s_ctr;
     __shared__ uint32_t s_ovf;  // attempts that overflowed in this round
     const uint32_t t = threadIdx.x;
-    Ctr *const ctr = a.ctr;
+    Ctr *const c = &s_ctr;
+    word_t *const words = reinterpret_cast<word_t *>(a.ctr), *const s_words = reinterpret_cast<word_t *>(c);
+    unsigned long long x = 0;
     if (t < NSTAT * 64) {
-        unsigned long long x = fresh(&a.stat[((size_t)(t >> 6) * STAT_SPREAD + (t & 63u)) * STAT_PAD]);
+        x = fresh(&a.stat[((size_t)(t >> 6) * STAT_SPREAD + (t & 63u)) * STAT_PAD]);
         for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
-        if ((t & 63u) == 0) {
-            const int id = (int)(t >> 6);
-            if (id == STAT_WON) {
-                ctr->won = (uint32_t)x;
-            } else if (id == STAT_WALK_CAPS) {
-                ctr->walk_caps = (uint32_t)x;
-            } else if (id == STAT_DEFERRED) {
-                ctr->deferred = (uint32_t)x;
-            } else if (id == STAT_OVERFLOWS) {
-                s_ovf = (uint32_t)x - ctr->overflows;
-                ctr->overflows = (uint32_t)x;
-            } else {
-                unsigned long long *dst[STAT_WON] = {&ctr->attempts, &ctr->walk_steps, &ctr->orient, &ctr->orient_exact,
-                                                     &ctr->insphere, &ctr->insphere_exact, &ctr->perturbed,
-                                                     &ctr->cav_tets, &ctr->bnd_facets};
-                *dst[id] = x;
+    } else if (t >= ROLL_BLOCK - 64 && t - (ROLL_BLOCK - 64) < CTR_WORDS) {
+        s_words[t - (ROLL_BLOCK - 64)] = fresh(&words[t - (ROLL_BLOCK - 64)]);
+    }
+    __syncthreads();
+    if (t < NSTAT * 64 && (t & 63u) == 0) {
+        const int id = (int)(t >> 6);
+        if (id == STAT_WON) {
+            c->won = (uint32_t)x;
+        } else if (id == STAT_WALK_CAPS) {
+            c->walk_caps = (uint32_t)x;
+        } else if (id == STAT_DEFERRED) {
+            c->deferred = (uint32_t)x;
+        } else if (id == STAT_OVERFLOWS) {
+            s_ovf = (uint32_t)x - c->overflows;
+            c->overflows = (uint32_t)x;
+        } else {
+            switch (id) {
+            case STAT_ATTEMPTS: c->attempts = x; break;
+            case STAT_WALK: c->walk_steps = x; break;
+            case STAT_ORIENT: c->orient = x; break;
+            case STAT_ORIENT_EXACT: c->orient_exact = x; break;
+            case STAT_INSPHERE: c->insphere = x; break;
+            case STAT_INSPHERE_EXACT: c->insphere_exact = x; break;
+            case STAT_PERTURBED: c->perturbed = x; break;
+            case STAT_CAV_TETS: c->cav_tets = x; break;
+            default: c->bnd_facets = x; break;
             }
         }
     }
-    if (carry) carry_free(a, t, ROLL_BLOCK);
+    if (carry) carry_free(a, c, t, ROLL_BLOCK);
     __syncthreads();
     if (t == 0) {
-        const uint32_t fln = ctr->fl_n, take = fresh(&ctr->fl_take), freed = fresh(&ctr->fl_next);
-        const uint32_t next_n = fresh(&ctr->next_n);
-        ctr->ball_wins = fresh(&ctr->wins);
-        ctr->ball_fl_n = fln;
-        ctr->ball_tet_count = ctr->tet_count;
+        const uint32_t fln = c->fl_n, take = c->fl_take;
+        c->ball_wins = c->wins;
+        c->ball_fl_n = fln;
+        c->ball_tet_count = c->tet_count;
         if (take > fln) {
             // units beyond the free list were fresh pool slots (beyond the pool: never used)
-            const unsigned long long tc = (unsigned long long)ctr->tet_count + (take - fln);
-            ctr->tet_count = tc > a.tcap ? a.tcap : (uint32_t)tc;
+            const unsigned long long tc = (unsigned long long)c->tet_count + (take - fln);
+            c->tet_count = tc > a.tcap ? a.tcap : (uint32_t)tc;
         }
         const uint32_t left = take < fln ? fln - take : 0u;
-        const uint32_t nxt = min(freed, a.flcap), keep = min(left, a.flcap - nxt);
-        ctr->dropped += (freed - nxt) + (left - keep);
-        ctr->ndefer = 0;
-        ctr->fl_n = nxt + keep;
-        ctr->fl_take = 0;
-        ctr->fl_next = 0;
-        ctr->wins = 0;
+        const uint32_t nxt = min(c->fl_next, a.flcap), keep = min(left, a.flcap - nxt);
+        c->dropped += (c->fl_next - nxt) + (left - keep);
+        c->ndefer = 0;
+        c->fl_n = nxt + keep;
+        c->fl_take = 0;
+        c->fl_next = 0;
+        c->wins = 0;
         // those that try again lost to a conflict, or (rounds over overflowed attempts, whose
         // two lists are one) overflowed again
-        ctr->conflicts += next_n - (a.nnext_ptr == a.novf_ptr ? s_ovf : 0u);
-        *a.nnext_ptr += next_n;
-        ctr->next_n = 0;
-        *const_cast<uint32_t *>(a.ncand_ptr) = 0;  // the list this round read from is empty now
+        c->conflicts += c->next_n - (a.nnext_ptr == a.novf_ptr ? s_ovf : 0u);
+        s_words[a.nnext_ptr - reinterpret_cast<const uint32_t *>(a.ctr)] += c->next_n;
+        c->next_n = 0;
+        s_words[a.ncand_ptr - reinterpret_cast<const uint32_t *>(a.ctr)] = 0;  // the list this round read from is empty now
     }
-    if (!end.snap) return;
-    __threadfence_block();
     __syncthreads();
-    static_assert(sizeof(Ctr) % sizeof(uint32_t) == 0, "the snapshot is copied in words");
-    uint32_t *src = reinterpret_cast<uint32_t *>(ctr);
-    uint32_t *dst = reinterpret_cast<uint32_t *>(end.snap);
-    for (uint32_t k = t; k < sizeof(Ctr) / sizeof(uint32_t); k += ROLL_BLOCK) dst[k] = fresh(&src[k]);
-    __threadfence_system();
-    __syncthreads();
-    if (t == 0) __hip_atomic_store(end.seq, end.tag, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (t >= 64) return;
+    if (t < CTR_WORDS) {
+        words[t] = s_words[t];
+        if (end.snap) reinterpret_cast<word_t *>(end.snap)[t] = s_words[t];
+    }
+    if (end.snap && t == 0) __hip_atomic_store(end.seq, end.tag, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // What becomes of each attempt, one thread per attempt: winners are listed with the slots they
