@@ -3,11 +3,13 @@
 // The rounds of dt_insert.hip gain a few percent of the mesh's vertices each, whatever the
 // mesh's size, and a round on a small mesh lasts 60 to 85 us: the latency of its dependent
 // accesses to memory and of its launches.  From the four points of the initial tetrahedron to
-// 768 vertices that is about 100 to 140 rounds, 5 to 9 ms of every triangulation.  Here one
-// block per cloud takes the first 764 points of the insertion order (Sec. 2.3) with coordinates,
+// 576 vertices that is about 100 rounds, 5 to 8 ms of every triangulation.  Here one block per
+// cloud takes the first 572 points of the insertion order (Sec. 2.3) with coordinates,
 // tetrahedra and claims in LDS, where a barrier ends a round, and writes the mesh to the pool
-// once: about 110 rounds of 18 us (half of it the slowest of the 16 attempts of a round),
-// 2.0 ms.  1000 points 7.1 -> 4.0 ms, 2e4 points 15.1 -> 11.2 ms a pass.
+// once: about 85 rounds of 18 us (half of it the slowest of the 16 attempts of a round), 1.6 ms.
+// 1000 points 7.1 -> 4.0 ms, 2e4 points 15.1 -> 11.2 ms a pass when it came in.  Limits of 320,
+// 448, 576 and 768 vertices: 1000 points 3.99, 3.80, 3.73, 3.78 ms, 2e4 points 9.93, 9.73, 9.64,
+// 9.75, 64 clouds of 1000 to 2e5 points 71.9, 71.0, 70.8, 72.6.
 //
 // Only the fp64 filters run; an attempt they leave undecided, a cavity beyond the group's
 // lists, or a point still open when the tetrahedra no longer fit, stays a candidate of the
@@ -28,9 +30,9 @@ namespace {
 constexpr int SEED_THREADS = 512;
 constexpr int SEED_LANES = 32;  // lanes per insertion
 constexpr int SEED_GROUPS = SEED_THREADS / SEED_LANES;
-// LDS: 34 bytes per vertex, 20 per tetrahedron and 480 per group, 147 KB of 160 in all
-constexpr uint32_t SEED_VERTS = 768;
-constexpr uint32_t SEED_TETS = 5632;  // uniform clouds have about 6.6 per vertex at this size
+// LDS: 34 bytes per vertex, 20 per tetrahedron and 480 per group, 112 KB in all
+constexpr uint32_t SEED_VERTS = 576;
+constexpr uint32_t SEED_TETS = 4224;  // uniform clouds have about 6.6 per vertex at this size
 constexpr uint32_t SEED_CAV = 48, SEED_BND = 64;
 constexpr uint32_t SEED_ROUNDS = 8 * SEED_VERTS;  // far more than a run takes
 constexpr uint32_t SEED_WALK = 64;  // steps of a walk in one round; it goes on in the next

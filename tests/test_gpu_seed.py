@@ -19,8 +19,8 @@ def moment_curve(n, seed):
 
 
 @pytest.mark.parametrize("case,opts", [
-    (("uniform", 5), {}), (("uniform", 31), {}), (("uniform", 767), {}), (("uniform", 768), {}),
-    (("uniform", 769), {}), (("uniform", 2100), {}), (("uniform", 800), dict(index_bits=64)),
+    (("uniform", 5), {}), (("uniform", 31), {}), (("uniform", 575), {}), (("uniform", 576), {}),
+    (("uniform", 577), {}), (("uniform", 2100), {}), (("uniform", 800), dict(index_bits=64)),
     (("uniform", 900), dict(subdet_cache=True)), (("uniform", 3000), dict(capacity_tets=4096)),
     (("uniform", 1500), dict(seed=7, adaptive_curve=True)), (("moment", 300), {}), (("shell", 1200), {}),
     (("lattice", 700), {}), (("duplicates", 900), {})])
@@ -48,7 +48,7 @@ def test_seeded_mesh_matches_oracle(dtlib, oracle_mod, case, opts):
 
 def test_seeded_clouds_of_a_batch(dtlib, oracle_mod):
     say("seed: batch of clouds below, at and above the block's limit")
-    clouds = [uniform_points(n, 700 + n) + n for n in (4, 5, 40, 768, 769, 2500)] + [moment_curve(200, 9)]
+    clouds = [uniform_points(n, 700 + n) + n for n in (4, 5, 40, 576, 577, 2500)] + [moment_curve(200, 9)]
     off = np.concatenate([[0], np.cumsum([len(c) for c in clouds])]).astype(np.uint64)
     with dtlib.Triangulation() as tri:
         tri.insert_batch(np.ascontiguousarray(np.vstack(clouds)), off)
