@@ -184,9 +184,10 @@ struct dt_ctx {
     uint32_t nclouds = 0;
     bool batch = false;                  // the context holds a dt_insert_batch result
     DevBuf<Cloud> clouds;
-    // records and grid of each insertion call so far (single clouds): walk starts of later calls
+    // records and grid of the largest insertion call so far (single clouds): walk starts of
+    // later calls
     DevBuf<Cloud> past;
-    std::vector<uint64_t> past_size;
+    uint64_t past_n = 0;                 // its points, 0: none
     bool near_anchor = false;            // of the current call: see RoundArgs
     DevBuf<uint64_t> off, ch_start, ch_end;
     DevBuf<uint32_t> cloud_ch;
@@ -1245,20 +1246,11 @@ int insert_clouds(dt_ctx *c, const double *xyz, uint64_t n, const std::vector<ui
     // an appended call finds its walk starts among the vertices of the largest earlier call; where
     // the earlier points are at least half as many as the call's own, its walks start there at
     // once, as those of refinement candidates at their tetrahedra
-    if (!fresh && !hint && !c->past_size.empty()) {
-        const size_t k = (size_t)(std::max_element(c->past_size.begin(), c->past_size.end()) - c->past_size.begin());
-        HIPCHK(launch_append_anchor(c->V.p, base, n, c->past.p + k, c->vtet.p, c->anchor.p, c->stream));
-    }
+    if (!fresh && !hint && c->past_n)
+        HIPCHK(launch_append_anchor(c->V.p, base, n, c->past.p, c->vtet.p, c->anchor.p, c->stream));
     c->near_anchor = hint || (!fresh && 2 * base >= n);
     if (hint) HIPCHK(launch_hint_anchor(c->V.p, base, n, c->npoints, hint, c->anchor.p, c->stream));
     HIPCHK(hipMemsetAsync(c->lastt.p, 0xFF, n * sizeof(uint32_t), c->stream));
-    if (C == 1 && !c->arena) {
-        // this call's records and grid, for the calls after it
-        if ((rc = ensure(c, c->past, std::max<size_t>(c->past_size.size() + 1, 64), true))) return rc;
-        HIPCHK(hipMemcpyAsync(c->past.p + c->past_size.size(), c->clouds.p, sizeof(Cloud), hipMemcpyDeviceToDevice,
-                              c->stream));
-        c->past_size.push_back(n);
-    }
     c->call_clouds = C;
     c->lord = lord;
     c->exact_needed = false;
@@ -1361,7 +1353,15 @@ int insert_clouds(dt_ctx *c, const double *xyz, uint64_t n, const std::vector<ui
         HIPCHK(launch_seed(c->V.p, c->clouds.p, C, 0, c->lord + lv.start[0], lv.size[0], c->dup.p, c->T, c->wide,
                            c->tcap, c->vtet.p, c->ctr, c->subd, c->stat, c->logged ? c->log_att.p : nullptr,
                            (uint32_t)base, c->stream));
+    // this call's records and grid, for the calls after it (only now: a call refused above leaves
+    // no records)
+    const bool keep = C == 1 && !c->arena && n > c->past_n;
+    if (keep) {
+        if ((rc = ensure(c, c->past, 1))) return rc;
+        HIPCHK(hipMemcpyAsync(c->past.p, c->clouds.p, sizeof(Cloud), hipMemcpyDeviceToDevice, c->stream));
+    }
     if ((rc = sync_ctr(c))) return rc;
+    if (keep) c->past_n = n;
     if (seed) c->mesh_vertices += c->hctr->won;
     c->st.duplicates += c->hctr->dups;
     auto t1 = std::chrono::steady_clock::now();
@@ -1924,7 +1924,7 @@ int dt_clear(dt_ctx *c) {
     c->hctr = c->hring;
     c->grow_pending = false;
     c->npoints = c->nv = 0;
-    c->past_size.clear();
+    c->past_n = 0;
     c->have_mesh = false;
     c->mesh_vertices = 0;
     c->fl_idx = c->list_idx = c->ovf_idx = 0;

@@ -40,3 +40,17 @@ def test_many_small_calls(dtlib, oracle_mod):
             tri.insert(xyz[lo:hi])
         t, _ = tri.tets()
         assert_parity(oracle_mod, xyz, t.astype(np.int64), "90 calls")
+
+
+def test_refused_first_call(dtlib, oracle_mod):
+    """A first call that is refused leaves no records for the calls after it to start from."""
+    say("append: after a refused call")
+    line = np.outer(np.arange(5000.0), [1.0, 2.0, -1.0])
+    xyz = uniform_points(1300, 817)
+    with dtlib.Triangulation() as tri:
+        with pytest.raises(dtlib.DTError):
+            tri.insert(line)
+        tri.insert(xyz[:300])
+        tri.insert(xyz[300:])
+        t, _ = tri.tets()
+    assert_parity(oracle_mod, xyz, t.astype(np.int64), "after a refused call")
