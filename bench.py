@@ -545,9 +545,9 @@ def run_uniform(args, xyz, n, seed, steps, warmup, progress):
     ball_per_ins = ball_bytes_per_insertion(F)
     ball_ach = ball_per_ins * agg["won"] / max(agg["ball_launches"], 1) / (ball_ms / 1000.0) / 1e9 if ball_ms > 0 else 0.0
     ball = {"bound": "hbm", "unit": "GB/s", "peak": peak,
-            "kernel": ("k_ball, 1024-thread blocks, " + ("64 lanes per candidate in rounds below 32768 candidates, "
-                                                        "16 above" if not lanes else
-                                                        f"{64 if lanes == 64 else 16} lanes per candidate")),
+            "kernel": ("k_select, k_roll and k_ball, " + ("64 lanes per winner in rounds below 32768 candidates, "
+                                                         "16 above" if not lanes else
+                                                         f"{64 if lanes == 64 else 16} lanes per winner")),
             "achieved": round(ball_ach, 2), "frac": round(ball_ach / peak, 5),
             "bytes_per_insertion": round(ball_per_ins, 1), "avg_launch_ms": round(ball_ms, 4)}
     detail = {"rounds_per_step": agg["rounds"] / steps, "attempts_per_point": agg["attempts"] / max(n * steps, 1),

@@ -57,9 +57,14 @@ typedef struct {
     uint32_t cavity_cap;    /* cavity tetrahedra buffered per insertion; 0: automatic     */
     uint64_t capacity_tets; /* initial tetrahedron pool (grown on demand); 0: automatic   */
     uint64_t seed;          /* seed of the randomized insertion levels (BRIO, Sec. 2.3)  */
-    uint32_t max_rounds;    /* 0: unlimited; otherwise DT_E_INCOMPLETE beyond it          */
+    uint32_t max_rounds;    /* 0: unlimited; otherwise DT_E_INCOMPLETE beyond it.  A new mesh's
+                               first insertions (up to 576 vertices) run in one launch
+                               that is no round, but as rounds when this, round_size or
+                               timing 1 is given                                          */
     int timing;             /* 1: time the two insertion kernels of every round with HIP
-                               events (three per round); 2: the cavity kernel of rounds of
+                               events (three per round; the second interval holds the
+                               selection of the winners, the DelaunayBall kernel and the
+                               round end); 2: the cavity kernel of rounds of
                                at least 32768 candidates only (two per such round: an
                                event record leaves the GPU idle for a few microseconds,
                                which short rounds feel most)                             */
@@ -102,11 +107,12 @@ typedef struct {
                                16 cavity tetrahedra per breadth-first step) or 256 (a
                                256-thread block, 64 per step); 0: automatic (256)        */
     int graph_rounds;       /* 1: launch each regular round (the candidate fill, both cavity
-                               passes, the DelaunayBall kernel and the three round-end
-                               kernels) as one HIP graph, built once per launch shape and
-                               given each round's arguments and grids; rounds for large
-                               cavities, timed rounds and traced rounds stay separate
-                               launches.  0: separate launches.  The result is the same.  */
+                               passes and the list between them, the selection, the round
+                               end and the DelaunayBall kernel) as one HIP graph, built
+                               once per launch shape and given each round's arguments and
+                               grids; rounds for large cavities, timed rounds and traced
+                               rounds stay separate launches.  0: separate launches.  The
+                               result is the same.                                        */
 } dt_options;
 
 enum { DT_SCHED_PLAIN = 0, DT_SCHED_LEARNED = 1 };

@@ -1299,13 +1299,13 @@ __global__ __launch_bounds__(ROLL_BLOCK) void k_select_roll(RoundArgs a, uint32_
 
 // ------------------------------------------------------------------ DelaunayBall
 
-// Winner test, slot reservation and DelaunayBall (Sec. 2.5), GL lanes per candidate, all in
-// one wave.  An attempt wins iff it completed its cavity and is not marked as lost (see the
-// head of this file); winners have disjoint cavities and no cavity meets another winner's
-// outer tetrahedra, so they build concurrently without further coordination.  Reading the one
-// mark instead of the claim words of every cavity and outer tetrahedron (about 47 random
-// records) and building in registers took the launches of about 79,000 candidates on 1e7
-// uniform points from 303 to 201 us; the kernel waits on its random 64-byte records.
+// DelaunayBall (Sec. 2.5) of the round's winners, which k_select has listed with their first
+// slots: GL lanes per winner, of one wave or the whole block.  Winners have disjoint cavities
+// and no cavity meets another winner's outer tetrahedra, so they build concurrently without
+// further coordination; blocks share nothing.  The kernel waits on its random 64-byte records.
+// Launches of about 79,000 candidates on 1e7 uniform points: 303 us with the winner test by the
+// claim words of every cavity and outer tetrahedron (about 47 random records) and boundaries in
+// memory, 201 us with the test by marks and boundaries in registers, 175 us over winners only.
 //
 // The ball takes the cavity's own slots (and F - C more when it is larger).  The
 // tetrahedron on boundary facet f of cavity tetrahedron k is k with vertex f replaced by p
@@ -1323,8 +1323,8 @@ __global__ __launch_bounds__(ROLL_BLOCK) void k_select_roll(RoundArgs a, uint32_
 // edge table entries per candidate; balls of up to half as many facets use it (load <= 3/4)
 __host__ __device__ constexpr int ball_table_bits(int GL) { return GL == 16 ? 7 : (GL == 64 ? 9 : 12); }
 constexpr unsigned long long HT_EMPTY = ~0ull;
-// threads per block of the ball kernel: the slot reservation is one atomic per block on one
-// counter, so larger blocks contend less (at the cost of LDS occupancy)
+// threads per block of the ball kernel: no counter is shared, and small blocks leave a compute
+// unit as soon as their own winners are built
 constexpr int BALL_BLOCK = 256;
 
 // orders the memory accesses of one group (part of one wave, or the whole block) across phases

@@ -313,8 +313,8 @@ struct RoundEnd {
 hipError_t launch_round(const RoundArgs &a, bool wide, uint32_t max_cand, uint32_t lanes, uint32_t large_lanes,
                         bool exact, const RoundEnd &end, hipStream_t s, hipEvent_t *ev);
 // A regular round (cavity buffers of the regular size) as one HIP graph: the fill, the two
-// cavity passes, the selection, DelaunayBall and round-end kernels as a chain of kernel
-// nodes.  The graph is built and instantiated once per launch shape (pool layout, lanes per
+// cavity passes with the list between them, the selection, round-end and DelaunayBall kernels as
+// a chain of kernel nodes.  The graph is built and instantiated once per launch shape (pool layout, lanes per
 // insertion); each later round of that shape only updates the nodes' arguments and grids.
 struct FillArgs {
     const uint32_t *lvl_start, *lvl_size, *lvl_bits;
