@@ -530,7 +530,8 @@ def run_uniform(args, xyz, n, seed, steps, warmup, progress):
     default_launch = (not lanes and not args.round_fraction and not args.round_size and n == 10_000_000
                       and seed == 1007 and not args.subdet_cache and not args.adaptive_curve and not args.walk_cap)
     kname = (f"k_cavity_g filter pass (and exact pass once launched), {lanes} lanes, rounds of 32768 candidates or more" if lanes else
-             "k_cavity_g filter pass (and exact pass once launched), 16 lanes, rounds of 32768 candidates or more")
+             "k_cavity_g filter pass (and exact pass once launched), 16 lanes (64 below 49152 candidates), "
+             "rounds of 32768 candidates or more")
     roofline = {"bound": "hbm", "kernel": kname, "achieved": round(achieved, 2), "peak": peak,
                 "unit": "GB/s", "frac": round(achieved / peak, 5),
                 # measured HBM bytes per launch (counter summary), only for the launch it was taken on
@@ -545,7 +546,7 @@ def run_uniform(args, xyz, n, seed, steps, warmup, progress):
     ball_per_ins = ball_bytes_per_insertion(F)
     ball_ach = ball_per_ins * agg["won"] / max(agg["ball_launches"], 1) / (ball_ms / 1000.0) / 1e9 if ball_ms > 0 else 0.0
     ball = {"bound": "hbm", "unit": "GB/s", "peak": peak,
-            "kernel": ("k_select, k_roll and k_ball, " + ("64 lanes per winner in rounds below 32768 candidates, "
+            "kernel": ("k_select, k_roll and k_ball, " + ("64 lanes per winner in rounds below 49152 candidates, "
                                                          "16 above" if not lanes else
                                                          f"{64 if lanes == 64 else 16} lanes per winner")),
             "achieved": round(ball_ach, 2), "frac": round(ball_ach / peak, 5),

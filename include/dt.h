@@ -70,10 +70,10 @@ typedef struct {
                                which short rounds feel most)                             */
     double round_fraction;  /* round size as a fraction of the current vertex count;
                                0: automatic (1/16, and 3/32 for rounds that stay below
-                               32768 candidates)                                         */
+                               49152 candidates)                                         */
     uint32_t lanes_per_insert; /* lanes of a wavefront cooperating on one insertion in the
                                   walk and cavity search: 4, 8, 16, 32 or 64 in every
-                                  round; 0: automatic (64 in rounds of fewer than 32768
+                                  round; 0: automatic (64 in rounds of fewer than 49152
                                   candidates, whose time is their slowest insertion's,
                                   16 in larger ones)                                     */
     int scheduler;          /* DT_SCHED_PLAIN (0) or DT_SCHED_LEARNED (1: uses the model of

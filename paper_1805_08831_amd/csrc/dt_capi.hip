@@ -35,8 +35,16 @@ constexpr double DEFAULT_ROUND_FRACTION = 1.0 / 16.0;
 constexpr uint32_t DEFAULT_WALK_CAP = 16;
 constexpr uint32_t DEFAULT_LARGE_LANES = 256;
 // automatic lanes: rounds of fewer candidates than this use 64 lanes per insertion; with the
-// automatic round fraction they take 1.5 times the usual share of the mesh's vertices
-constexpr uint32_t SMALL_ROUND = 32768;
+// automatic round fraction they take 1.5 times the usual share of the mesh's vertices.  16 lanes
+// need fewer instructions per insertion, 64 a shorter chain; the last, partly filled pass over
+// the chip weighs less the larger the round.  A pass with limits of 24576, 32768, 49152, 57344,
+// 65536 and 98304: 1e6 points 35.5, 34.4, 33.4, 33.3, 33.7, 34.4 ms; 1e7 144.0, 143.0, 141.8,
+// 141.7, 141.6, 142.0; 64 clouds of 1000 to 2e5 points 71.7, 70.8, 69.6, 70.2, 71.7, 73.5;
+// 2.5e5 points refined sixfold 69.6, 69.0, 68.3, 68.9, 68.6, 70.1.  32 lanes between 49152 and
+// 131072: 33.7, 142.4, 71.4, 69.8.
+constexpr uint32_t SMALL_ROUND = 49152;
+// timing 2: rounds of at least this many candidates are timed
+constexpr uint32_t TIMED_ROUND = 32768;
 constexpr double SHORT_ROUND_FRACTION_SCALE = 1.5;
 constexpr uint32_t ROUND_MIN = 256;
 constexpr uint32_t DRAIN_SLICE = 4096;  // candidates per round when draining overflowed cavities
@@ -624,10 +632,10 @@ int enqueue_round(dt_ctx *c, int ci, int ni, int oi, uint32_t max_cand, uint32_t
     }
     c->round_counter++;
     // timing 1: events around both kernels in every round; 2: around the cavity kernel in
-    // rounds of at least SMALL_ROUND candidates (each event record leaves the GPU idle for a
+    // rounds of at least TIMED_ROUND candidates (each event record leaves the GPU idle for a
     // few microseconds, which the short rounds would feel most)
     hipEvent_t evs[3] = {c->ev[slot][0], c->ev[slot][1], c->opt.timing == 1 ? c->ev[slot][2] : nullptr};
-    const bool timed = c->opt.timing == 1 || (c->opt.timing == 2 && max_cand >= SMALL_ROUND);
+    const bool timed = c->opt.timing == 1 || (c->opt.timing == 2 && max_cand >= TIMED_ROUND);
     c->slot_timed[slot] = timed;
     // automatic lanes: a wavefront per insertion in short rounds, which wait on their slowest
     // candidate, c->lanes in the rest
