@@ -47,6 +47,8 @@ constexpr uint32_t SMALL_ROUND = 49152;
 constexpr uint32_t TIMED_ROUND = 32768;
 constexpr double SHORT_ROUND_FRACTION_SCALE = 1.5;
 constexpr uint32_t ROUND_MIN = 256;
+// clouds of a call whose first insertions run in one block each (dt_seed.hip)
+constexpr uint32_t SEED_FEW_CLOUDS = 64, SEED_MAX_CLOUDS = 1024, SEED_MEAN_POINTS = 16;
 constexpr uint32_t DRAIN_SLICE = 4096;  // candidates per round when draining overflowed cavities
 constexpr uint32_t EXPORT_CHUNK = 1u << 24;  // slots per staged export launch (a multiple of 64)
 constexpr size_t TET_BYTES = 64;               // one tetrahedron record, either layout
@@ -1355,8 +1357,14 @@ int insert_clouds(dt_ctx *c, const double *xyz, uint64_t n, const std::vector<ui
         c->log_n = n;
     }
     // the first insertions of a new mesh in one block per cloud.  Not under options that speak of
-    // rounds: a limit or a size of rounds, or every round timed.
-    const bool seed = fresh && c->opt.max_rounds == 0 && c->opt.round_size == 0 && c->opt.timing != 1;
+    // rounds: a limit or a size of rounds, or every round timed.  Not for many clouds, whose first
+    // rounds fill the chip by themselves while their blocks, one to a compute unit, queue up
+    // (with against without: clouds of 200 points, 256 of them 1.8 against 5.4 ms a call, 1024 4.6
+    // against 7.5, 4096 16.4 against 12.5; of 2000 points, 1024 26.1 against 30.8, 4096 85.6 against
+    // 83.0; of 30 points, 1024 1.8 against 2.4, 2048 2.8 against 2.5), nor for more than a few tiny
+    // ones, done in a few rounds (of 8 points, 64 0.37 against 0.39, 256 0.77 against 0.49).
+    const bool seed = fresh && c->opt.max_rounds == 0 && c->opt.round_size == 0 && c->opt.timing != 1 &&
+                      (C <= SEED_FEW_CLOUDS || (C <= SEED_MAX_CLOUDS && n >= (uint64_t)SEED_MEAN_POINTS * C));
     if (seed)
         HIPCHK(launch_seed(c->V.p, c->clouds.p, C, 0, c->lord + lv.start[0], lv.size[0], c->dup.p, c->T, c->wide,
                            c->tcap, c->vtet.p, c->ctr, c->subd, c->stat, c->logged ? c->log_att.p : nullptr,

@@ -56,3 +56,18 @@ def test_seeded_clouds_of_a_batch(dtlib, oracle_mod):
             t, nb = tri.tets_batch(k)
             assert_parity(oracle_mod, c, t.astype(np.int64), f"cloud {k}")
             check_invariants(c, t.astype(np.int64), nb, oracle_mod, expect_vertices=np.arange(len(c)))
+
+
+@pytest.mark.parametrize("clouds,points", [(64, 6), (65, 15), (65, 16), (1024, 18), (1025, 18)])
+def test_batches_around_the_limits(dtlib, oracle_mod, clouds, points):
+    """Both sides of the rule on the number of clouds and their mean size."""
+    say(f"seed: {clouds} clouds of {points} points")
+    xyz = uniform_points(clouds * points, 47 + clouds + points)
+    off = np.arange(clouds + 1, dtype=np.uint64) * points
+    with dtlib.Triangulation() as tri:
+        tri.insert_batch(xyz, off)
+        for k in sorted({0, 1, clouds // 2, clouds - 1}):
+            c = xyz[k * points:(k + 1) * points]
+            t, nb = tri.tets_batch(k)
+            assert_parity(oracle_mod, c, t.astype(np.int64), f"cloud {k} of {clouds}")
+            check_invariants(c, t.astype(np.int64), nb, oracle_mod, expect_vertices=np.arange(points))
