@@ -185,6 +185,8 @@ struct dt_ctx {
     uint32_t slot_cand[3] = {}, slot_capC[3] = {};
     bool slot_timed[3] = {};  // the round in the slot recorded timing events
     bool grow_pending = false;  // a round found the pool full: grow before the next one
+    // test hook: error bits set before the next round's kernels and behind its last one
+    uint32_t raise_before = 0, raise_behind = 0;
     dt_stats st{};
     uint32_t trace_prev_won = 0, trace_prev_conf = 0, trace_prev_ovf = 0;
     uint64_t trace_rounds = 0;
@@ -512,8 +514,9 @@ int check_errors(dt_ctx *c) {
     uint32_t e = c->hctr->error;
     if (e & ERR_POOL) {
         // some insertions found the pool full and will retry: the pool grows before the next
-        // round is planned (once no round is in flight)
-        HIPCHK(hipMemsetAsync(&c->ctr->error, 0, sizeof(uint32_t), c->stream));
+        // round is planned (once no round is in flight).  Only this bit is cleared: the balls of
+        // the rounds launched so far, built behind their snapshots, may have raised others
+        HIPCHK(launch_error_bits(c->ctr, 0, ERR_POOL, c->stream));
         c->hctr->error &= ~ERR_POOL;
         e &= ~ERR_POOL;
         c->grow_pending = true;
@@ -653,6 +656,9 @@ int enqueue_round(dt_ctx *c, int ci, int ni, int oi, uint32_t max_cand, uint32_t
         end.seq = &c->hseq[slot];
         end.tag = c->slot_tag[slot];
     }
+    const uint32_t raise_before = c->raise_before, raise_behind = c->raise_behind;
+    c->raise_before = c->raise_behind = 0;
+    if (raise_before) HIPCHK(launch_error_bits(d, raise_before, 0, c->stream));
     if (graph) {
         const FillPlan none{};
         const FillArgs nofill{nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
@@ -660,6 +666,7 @@ int enqueue_round(dt_ctx *c, int ci, int ni, int oi, uint32_t max_cand, uint32_t
         c->fl_idx ^= 1;
         HIPCHK(launch_round_graph(c->graphs, plan ? *plan : none, fa ? *fa : nofill, a, c->wide, max_cand, lanes, end,
                                   c->stream));
+        if (raise_behind) HIPCHK(launch_error_bits(d, raise_behind, 0, c->stream));
         c->slot_cand[slot] = max_cand;
         c->slot_capC[slot] = capC;
         c->st.rounds++;
@@ -672,6 +679,7 @@ int enqueue_round(dt_ctx *c, int ci, int ni, int oi, uint32_t max_cand, uint32_t
                                 fa->vtet, fa->cand_pt, fa->cand_rank, fa->ncand, c->stream));
     HIPCHK(launch_round(a, c->wide, max_cand, lanes, c->large_lanes, c->exact_needed, end, c->stream,
                         timed ? evs : nullptr));
+    if (raise_behind) HIPCHK(launch_error_bits(d, raise_behind, 0, c->stream));
     c->fl_idx ^= 1;
     if (!c->ring_direct) {
         HIPCHK(hipMemcpyAsync(&c->hring[slot], c->ctr, sizeof(Ctr), hipMemcpyDeviceToHost, c->stream));
@@ -1391,7 +1399,12 @@ int insert_clouds(dt_ctx *c, const double *xyz, uint64_t n, const std::vector<ui
     if ((rc = ensure_round_buffers(c, (uint32_t)std::min<uint64_t>(want_r, std::max<uint64_t>(n, ROUND_MIN)))))
         return rc;
     rc = run_rounds(c, lv, d_start, d_size, d_bits, d_rb, base, n);
-    if (rc == DT_OK) HIPCHK(hipStreamSynchronize(c->stream));  // the last round's balls
+    // a round's balls are built behind its snapshot of the counters, and what they raise is in the
+    // next round's: after the last round the counters are read once more
+    if (rc == DT_OK || rc == DT_E_INCOMPLETE) {
+        int e;
+        if ((e = sync_ctr(c)) || (e = check_errors(c))) rc = e;
+    }
     auto t2 = std::chrono::steady_clock::now();
     c->st.ms_sort += std::chrono::duration<double, std::milli>(t1 - t0).count();
     c->st.ms_insert += std::chrono::duration<double, std::milli>(t2 - t1).count();
@@ -2467,6 +2480,15 @@ int dt_refine(dt_ctx *c, double h, uint32_t max_steps, uint32_t *step_counts, ui
 int dt_debug_widen_at(dt_ctx *c, uint64_t slots) {
     if (!c || slots < 4096 || slots > MAX_TETS) return DT_E_ARG;
     c->narrow_max = slots;
+    return DT_OK;
+}
+
+// Not in the public header: error bits (ERR_*) raised around the next round's kernels, as if the
+// selection (before) or the balls (behind) of that round had raised them.
+int dt_test_raise(dt_ctx *c, uint32_t before, uint32_t behind) {
+    if (!c) return DT_E_ARG;
+    c->raise_before = before;
+    c->raise_behind = behind;
     return DT_OK;
 }
 

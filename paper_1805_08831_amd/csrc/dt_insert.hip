@@ -1800,6 +1800,16 @@ hipError_t launch_reset_claims(void *T, bool wide, uint32_t tcap, hipStream_t s)
     return hipGetLastError();
 }
 
+// Sets and clears bits of the counters' error word, behind whatever the stream holds.
+__global__ void k_error_bits(Ctr *__restrict__ ctr, uint32_t set, uint32_t clear) {
+    ctr->error = (ctr->error | set) & ~clear;
+}
+
+hipError_t launch_error_bits(Ctr *ctr, uint32_t set, uint32_t clear, hipStream_t s) {
+    k_error_bits<<<1, 1, 0, s>>>(ctr, set, clear);
+    return hipGetLastError();
+}
+
 // A pool with 32-bit codes copied into one with 64-bit codes (the code 4 t + f is the same
 // number in either width).
 __global__ void k_widen(const Tet *__restrict__ src, TetW *__restrict__ dst, uint32_t count) {
