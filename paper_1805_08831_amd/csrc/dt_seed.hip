@@ -457,6 +457,7 @@ __global__ __launch_bounds__(SEED_THREADS) void k_seed(const Vert *__restrict__ 
                                 }
                             }
                     }
+                    if (open) atomicOr(&ctr->error, ERR_WALK);  // a pivot without an end: never expected
                 }
             }
             __asm__ volatile("" ::: "memory");

@@ -64,3 +64,12 @@ def test_errors_beside_a_limit_of_rounds(dtlib):
         tri.insert(xyz[:5])
         raise_bits(dtlib, tri, 0, ERR_WALK)
         expect_internal(dtlib, tri, xyz[5:])
+
+
+@pytest.mark.parametrize("points", [5, 300, 2000])
+def test_errors_before_the_first_round(dtlib, points):
+    """As the first insertions (csrc/dt_seed.hip) raise them, ahead of every round."""
+    say(f"error ahead of the first round, {points} points")
+    with dtlib.Triangulation() as tri:
+        raise_bits(dtlib, tri, ERR_WALK, 0)
+        expect_internal(dtlib, tri, uniform_points(points, 934))
