@@ -1399,9 +1399,10 @@ int insert_clouds(dt_ctx *c, const double *xyz, uint64_t n, const std::vector<ui
     if ((rc = ensure_round_buffers(c, (uint32_t)std::min<uint64_t>(want_r, std::max<uint64_t>(n, ROUND_MIN)))))
         return rc;
     rc = run_rounds(c, lv, d_start, d_size, d_bits, d_rb, base, n);
-    // a round's balls are built behind its snapshot of the counters, and what they raise is in the
-    // next round's: after the last round the counters are read once more
-    if (rc == DT_OK || rc == DT_E_INCOMPLETE) {
+    // a round's balls are built behind the snapshot that its round end writes, and what they raise is
+    // in the next round's: after the last round the counters are read once more (snapshots that are
+    // copies are taken behind the balls)
+    if (c->ring_direct && (rc == DT_OK || rc == DT_E_INCOMPLETE)) {
         int e;
         if ((e = sync_ctr(c)) || (e = check_errors(c))) rc = e;
     }
