@@ -296,7 +296,7 @@ int dt_get_points(dt_ctx *ctx, double *xyz, uint64_t *num_points);
    other errors as dt_insert_points.  Calls on one device share the array: calls that
    overlap on one device race.  No context, no statistics. */
 #define DT_NOALLOC_MAX_POINTS 65536u
-#define DT_NOALLOC_SCRATCH_BYTES (128u << 20)
+#define DT_NOALLOC_SCRATCH_BYTES (129u << 20)
 int dt_triangulate_noalloc(int device, void *stream, const double *xyz, uint64_t n, uint32_t *tets,
                            int64_t *nbrs, uint64_t *num_tets);
 

@@ -2103,6 +2103,10 @@ int dt_debug_set_round_counter(dt_ctx *c, uint64_t rounds) {
 
 }  // extern "C"
 
+// 128 MiB, and 1 MiB for buffers that came later: lists of the winners and of the lost attempts
+// (12 bytes a candidate of a round, 48 KiB), four more spread statistics (32 KiB), the box
+// reduction's chunks (3 KiB) and the packed words of the export (a quarter of a byte per slot, at
+// most 0.5 MiB for the slots that fit).  What fitted 128 MiB without them still fits.
 static __device__ __align__(256) unsigned char scratch[DT_NOALLOC_SCRATCH_BYTES];
 
 namespace {
