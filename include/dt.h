@@ -323,8 +323,9 @@ int dt_debug_sort(dt_ctx *ctx, const double *xyz, uint64_t n, uint64_t *keys, ui
                   int *moore_m);
 
 /* Sets the context's round counter (the stamp of the next round's claims).  Claim stamps
-   take the low 32 bits of the counter; when they wrap, the library resets every claim word
-   before the round.  Lets a test cross the wrap without 2^32 rounds. */
+   take the low 16 bits of the counter; when they wrap (every 65536 rounds), the library resets
+   every claim word before the round.  The marks of lost attempts take 31 bits and are cleared
+   when those wrap.  Lets a test cross either wrap without that many rounds. */
 int dt_debug_set_round_counter(dt_ctx *ctx, uint64_t rounds);
 
 /* With dt_options.index_bits = 0, a pool with 32-bit codes is widened to 64-bit codes when

@@ -1,7 +1,7 @@
 // Concurrent Bowyer-Watson insertion rounds (paper Sec. 2.1 Algorithm 1, Sec. 2.5, Sec. 2.6;
 // concurrency rules of Sec. 3.2).
 //
-// A round is two kernels over the round's candidate points:
+// A round is a chain of kernels over the round's candidate points:
 //   k_cavity_g : Walk (visibility walk, Sec. 2.1) from a live tetrahedron of an already
 //              inserted neighbour on the space-filling curve, then Cavity (breadth-first
 //              search by perturbed insphere, ghosts by the half-space + circumdisk rule of
@@ -10,22 +10,26 @@
 //              tetrahedron's 64-bit claim word: its stamp S (see claim_stamp) for cavity
 //              tetrahedra, S + 1 for tetrahedra found outside.  Meeting a lower claim that
 //              excludes it ends the attempt (one search step later); displacing the cavity
-//              claim of a later attempt marks that attempt as lost.
-//   k_ball   : an attempt wins iff it completed its cavity and nobody marked it.  If two
+//              claim of a later attempt marks that attempt as lost.  A first pass decides signs
+//              by the fp64 filter only; once a call has needed it, k_defer lists the attempts
+//              left undecided and a second pass runs them with exact predicates.
+//   k_select : an attempt wins iff it completed its cavity and nobody marked it.  If two
 //              attempts share a cavity tetrahedron, or one's cavity touches the other's outer
 //              tetrahedra, the later one has lost: some tetrahedron of its cavity is claimed
 //              by the earlier one too (adjacency runs both ways), and on that word either it
 //              found a lower claim itself or its claim was displaced by a lower one.  So the
 //              cavities of winners are disjoint from each other and from each other's adjacent
 //              tetrahedra (rules 1a-1c and 2 of Sec. 3.2); the first in the order of a
-//              round always wins, so every round makes progress.  A winner builds
-//              DelaunayBall (Sec. 2.5): one tetrahedron per boundary facet, glued a priori to
-//              the outer tetrahedron, and glued to its three sibling tetrahedra through an
-//              LDS table of boundary edges (pivoting around each boundary edge through copies
-//              of the cavity tetrahedra for large balls).  Freed
-//              slots are reused in later rounds (Sec. 2.5 end, Sec. 3.6).
-// The ball kernel queues losers for the next round with their rank, and overflowing cavities
-// for rounds with larger per-insertion buffers; k_roll ends the round.
+//              round always wins, so every round makes progress.  Winners are listed with their
+//              slots; losers are queued for the next round with their rank, and overflowing
+//              cavities for rounds with larger per-insertion buffers.
+//   k_roll   : ends the round: counters advanced and written to the host, which plans on.  (Both
+//              in one launch, k_select_roll, in short rounds.)
+//   k_ball   : each winner builds DelaunayBall (Sec. 2.5): one tetrahedron per boundary facet,
+//              glued a priori to the outer tetrahedron, and glued to its three sibling
+//              tetrahedra through an LDS table of boundary edges (pivoting around each boundary
+//              edge through copies of the cavity tetrahedra for large balls).  Freed slots are
+//              reused in later rounds (Sec. 2.5 end, Sec. 3.6).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -1292,7 +1296,9 @@ __global__ __launch_bounds__(ROLL_BLOCK) void k_select_roll(RoundArgs a, uint32_
         select_attempts<K>(a, i0 + threadIdx.x);
         __syncthreads();
     }
-    __threadfence_block();  // this wave's atomics have been performed
+    // the counters and statistics that this block's atomics have changed are read by the same block,
+    // at the atomics' own scope (see fresh): behind the barrier it finds their values
+    __threadfence_block();
     __syncthreads();
     roll_counters(a, carry != 0, end);
 }
@@ -1317,7 +1323,8 @@ __global__ __launch_bounds__(ROLL_BLOCK) void k_select_roll(RoundArgs a, uint32_
 // hash table of edges in LDS, and each record is stored once it is complete (one row of
 // vertices, one of neighbours).  Balls too large for the table (64 facets with 16 lanes, 256
 // with 64, 2048 with the whole block) pair siblings by pivoting around the edge through copies
-// of the cavity tetrahedra in memory instead, a chain of dependent loads for every edge.  In
+// of the cavity tetrahedra in memory instead, a chain of dependent loads for every edge (hardly
+// ever with 64 lanes: the regular rounds' buffers hold 213 facets at the default capacity).  In
 // rounds for large cavities (170 tetrahedra on average on mixed points) one wavefront per ball
 // and pivots beyond 64 facets took 146 us a launch.
 // edge table entries per candidate; balls of up to half as many facets use it (load <= 3/4)
@@ -1371,7 +1378,7 @@ __global__ __launch_bounds__(BS) void k_ball(RoundArgs a) {
     const uint32_t gl = threadIdx.x % GL;
     const uint32_t gi = threadIdx.x / GL;
     const uint32_t wi = blockIdx.x * GPB + gi;
-    if (wi >= a.ctr->ball_wins) return;  // whole groups; no barrier below
+    if (wi >= a.ctr->ball_wins) return;  // whole groups: where a barrier follows, the whole block
     const unsigned long long tb0 = a.clk ? (unsigned long long)wall_clock64() : 0ull;
     const uint2 rec = a.wins[wi];
     const uint32_t i = rec.x, u0 = rec.y;
@@ -1718,7 +1725,10 @@ int lanes_index(uint32_t lanes) {
 
 }  // namespace
 
-// The kernels and grids are those of launch_fill_list and launch_round (regular rounds); an empty fill plan runs one block that appends nothing.
+// The kernels and grids are those of launch_fill_list and launch_round (regular rounds), but for the
+// chain's fixed shape: the exact pass is always there and always has EXACT_LANES lanes (launch_round
+// gives it 64 where the filter pass has 64), selection and round end are always two launches.  An
+// empty fill plan runs one block that appends nothing.
 hipError_t launch_round_graph(RoundGraph *graphs, const FillPlan &plan, const FillArgs &fa, const RoundArgs &a,
                               bool wide, uint32_t max_cand, uint32_t lanes, const RoundEnd &end, hipStream_t s) {
     if (max_cand == 0 || a.capC > LCAPC) return hipErrorInvalidValue;
@@ -1785,8 +1795,8 @@ void destroy_round_graphs(RoundGraph *graphs) {
     }
 }
 
-// Claim words back to the empty value (above every stamp), for the round after the round
-// counter's low 32 bits wrap.  A fill kernel rather than a strided memset.
+// Claim words back to the empty value (above every stamp), for the round at which the stamps' 16
+// bits of the round counter wrap.  A fill kernel rather than a strided memset.
 template <class R>
 __global__ void k_reset_claims(R *__restrict__ T, uint32_t tcap) {
     for (uint64_t t = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; t < tcap; t += (uint64_t)gridDim.x * blockDim.x)

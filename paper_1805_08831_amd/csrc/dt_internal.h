@@ -201,8 +201,8 @@ struct RoundArgs {
     uint32_t rank_shift;         // bits of the ranks left out of the stamps
     // if set (trace mode): [stride][8] per attempt.  Filter pass: wall clock (100 MHz) at its
     // start, at the walk's end and at its end, then walk steps | cavity steps << 16 | cavity
-    // size << 32 | status << 48.  Ball kernel: clock at its start, after the winner test and
-    // slot reservation, after the cavity copies and at its end.
+    // size << 32 | status << 48.  Ball kernel (winners only): clock at its start, once the winner's
+    // entry and counts are there, once its boundary (a large ball: its cavity) is and at its end.
     unsigned long long *clk;
 };
 
@@ -306,8 +306,9 @@ struct RoundEnd {
     unsigned long long *seq, tag;
     uint32_t free_slots;
 };
-// The kernels of a round: cavity passes, selection, round end (the counters are final before the
-// balls are built, so that the host plans on while they are), DelaunayBall.
+// The kernels of a round: cavity passes, selection, round end (the host's copy of the counters is
+// written before the balls are built, so that it plans on while they are; errors that the balls
+// raise are in the next copy), DelaunayBall.
 // exact: launch the exact-predicate pass after the filter pass of a regular round (without
 // it, attempts the filter hands on retry in the next round)
 hipError_t launch_round(const RoundArgs &a, bool wide, uint32_t max_cand, uint32_t lanes, uint32_t large_lanes,
