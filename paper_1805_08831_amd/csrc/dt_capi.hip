@@ -516,7 +516,7 @@ int check_errors(dt_ctx *c) {
         // some insertions found the pool full and will retry: the pool grows before the next
         // round is planned (once no round is in flight).  Only this bit is cleared: the balls of
         // the rounds launched so far, built behind their snapshots, may have raised others
-        HIPCHK(launch_error_bits(c->ctr, 0, ERR_POOL, c->stream));
+        HIPCHK(launch_error_bits(c->ctr, 0, ERR_POOL, nullptr, c->stream));
         c->hctr->error &= ~ERR_POOL;
         e &= ~ERR_POOL;
         c->grow_pending = true;
@@ -658,7 +658,7 @@ int enqueue_round(dt_ctx *c, int ci, int ni, int oi, uint32_t max_cand, uint32_t
     }
     const uint32_t raise_before = c->raise_before, raise_behind = c->raise_behind;
     c->raise_before = c->raise_behind = 0;
-    if (raise_before) HIPCHK(launch_error_bits(d, raise_before, 0, c->stream));
+    if (raise_before) HIPCHK(launch_error_bits(d, raise_before, 0, nullptr, c->stream));
     if (graph) {
         const FillPlan none{};
         const FillArgs nofill{nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr,
@@ -666,7 +666,7 @@ int enqueue_round(dt_ctx *c, int ci, int ni, int oi, uint32_t max_cand, uint32_t
         c->fl_idx ^= 1;
         HIPCHK(launch_round_graph(c->graphs, plan ? *plan : none, fa ? *fa : nofill, a, c->wide, max_cand, lanes, end,
                                   c->stream));
-        if (raise_behind) HIPCHK(launch_error_bits(d, raise_behind, 0, c->stream));
+        if (raise_behind) HIPCHK(launch_error_bits(d, raise_behind, 0, nullptr, c->stream));
         c->slot_cand[slot] = max_cand;
         c->slot_capC[slot] = capC;
         c->st.rounds++;
@@ -679,7 +679,7 @@ int enqueue_round(dt_ctx *c, int ci, int ni, int oi, uint32_t max_cand, uint32_t
                                 fa->vtet, fa->cand_pt, fa->cand_rank, fa->ncand, c->stream));
     HIPCHK(launch_round(a, c->wide, max_cand, lanes, c->large_lanes, c->exact_needed, end, c->stream,
                         timed ? evs : nullptr));
-    if (raise_behind) HIPCHK(launch_error_bits(d, raise_behind, 0, c->stream));
+    if (raise_behind) HIPCHK(launch_error_bits(d, raise_behind, 0, nullptr, c->stream));
     c->fl_idx ^= 1;
     if (!c->ring_direct) {
         HIPCHK(hipMemcpyAsync(&c->hring[slot], c->ctr, sizeof(Ctr), hipMemcpyDeviceToHost, c->stream));
@@ -1405,11 +1405,13 @@ int insert_clouds(dt_ctx *c, const double *xyz, uint64_t n, const std::vector<ui
         return rc;
     rc = run_rounds(c, lv, d_start, d_size, d_bits, d_rb, base, n);
     // a round's balls are built behind the snapshot that its round end writes, and what they raise is
-    // in the next round's: after the last round the counters are read once more (snapshots that are
+    // in the next round's: after the last round the error word is read once more (snapshots that are
     // copies are taken behind the balls)
     if (c->ring_direct && (rc == DT_OK || rc == DT_E_INCOMPLETE)) {
-        int e;
-        if ((e = sync_ctr(c)) || (e = check_errors(c))) rc = e;
+        HIPCHK(launch_error_bits(c->ctr, 0, 0, &c->hctr->error, c->stream));
+        HIPCHK(hipStreamSynchronize(c->stream));
+        const int e = check_errors(c);
+        if (e) rc = e;
     }
     auto t2 = std::chrono::steady_clock::now();
     c->st.ms_sort += std::chrono::duration<double, std::milli>(t1 - t0).count();

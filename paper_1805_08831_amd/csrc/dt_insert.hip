@@ -1810,13 +1810,16 @@ hipError_t launch_reset_claims(void *T, bool wide, uint32_t tcap, hipStream_t s)
     return hipGetLastError();
 }
 
-// Sets and clears bits of the counters' error word, behind whatever the stream holds.
-__global__ void k_error_bits(Ctr *__restrict__ ctr, uint32_t set, uint32_t clear) {
-    ctr->error = (ctr->error | set) & ~clear;
+// Sets and clears bits of the counters' error word, behind whatever the stream holds; the result
+// also goes to `out` (pinned host memory, may be null): a launch takes less than a copy.
+__global__ void k_error_bits(Ctr *__restrict__ ctr, uint32_t set, uint32_t clear, uint32_t *__restrict__ out) {
+    const uint32_t e = (ctr->error | set) & ~clear;
+    ctr->error = e;
+    if (out) *out = e;
 }
 
-hipError_t launch_error_bits(Ctr *ctr, uint32_t set, uint32_t clear, hipStream_t s) {
-    k_error_bits<<<1, 1, 0, s>>>(ctr, set, clear);
+hipError_t launch_error_bits(Ctr *ctr, uint32_t set, uint32_t clear, uint32_t *out, hipStream_t s) {
+    k_error_bits<<<1, 1, 0, s>>>(ctr, set, clear, out);
     return hipGetLastError();
 }
 

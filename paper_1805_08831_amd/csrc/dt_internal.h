@@ -336,7 +336,7 @@ hipError_t launch_round_graph(RoundGraph *graphs, const FillPlan &plan, const Fi
                               bool wide, uint32_t max_cand, uint32_t lanes, const RoundEnd &end, hipStream_t s);
 void destroy_round_graphs(RoundGraph *graphs);
 hipError_t launch_reset_claims(void *T, bool wide, uint32_t tcap, hipStream_t s);
-hipError_t launch_error_bits(Ctr *ctr, uint32_t set, uint32_t clear, hipStream_t s);
+hipError_t launch_error_bits(Ctr *ctr, uint32_t set, uint32_t clear, uint32_t *out, hipStream_t s);
 // copies `count` Tet records into TetW records
 hipError_t launch_widen(const void *src, void *dst, uint32_t count, hipStream_t s);
 // export: live bit set (one word per 64 slots) with per-word counts, both packed with the scan of
