@@ -170,7 +170,8 @@ int dt_create(dt_ctx **out, const dt_options *opt);
    leaves the context empty.  After DT_E_ARG, DT_E_INPUT or DT_E_DEGENERATE the context
    is as it was before the call; after DT_E_CAPACITY, DT_E_INCOMPLETE, DT_E_DEVICE or
    DT_E_INTERNAL only dt_clear, dt_get_stats, dt_last_error and dt_destroy are
-   meaningful.  n = 0 does nothing and returns DT_OK.  Limits: fewer than 2^30 points per
+   meaningful (a call that failed among its rounds makes further insertions return DT_E_ARG
+   until dt_clear).  n = 0 does nothing and returns DT_OK.  Limits: fewer than 2^30 points per
    call and 2^31 in all (DT_E_CAPACITY); fewer than 2^30 tetrahedron slots with 32-bit
    adjacency codes, 2^32 - 16 with 64-bit codes (dt_options.index_bits). */
 int dt_insert_points(dt_ctx *ctx, const double *xyz, uint64_t n);

@@ -107,6 +107,7 @@ struct dt_ctx {
     uint64_t npoints = 0;  // points passed so far (global input indices)
     uint64_t nv = 0;       // vertex records in V
     bool have_mesh = false;
+    bool unfinished = false;  // a call ended inside its rounds: its candidates are still listed
     uint64_t round_counter = 0;  // monotonic over the context's lifetime
     uint64_t mesh_vertices = 0;
     int fl_idx = 0;
@@ -1208,6 +1209,9 @@ int level_order(dt_ctx *c, uint32_t *svals, const Vert *V, uint64_t n, uint64_t 
 // near the point, where its walk starts (its anchor)
 int insert_clouds(dt_ctx *c, const double *xyz, uint64_t n, const std::vector<uint64_t> &off,
                   const uint32_t *hint = nullptr) {
+    // the kernels index the call's arrays by record - vlo, and the candidates that a failed call
+    // has left in the lists are records before vlo
+    if (c->unfinished) return fail(c, DT_E_ARG, "an earlier insertion has failed: dt_clear the context first");
     const uint32_t C = (uint32_t)(off.size() - 1);
     auto t0 = std::chrono::steady_clock::now();
     HIPCHK(hipSetDevice(c->device));
@@ -1395,6 +1399,7 @@ int insert_clouds(dt_ctx *c, const double *xyz, uint64_t n, const std::vector<ui
     c->st.duplicates += c->hctr->dups;
     auto t1 = std::chrono::steady_clock::now();
     // 8. insertion rounds
+    c->unfinished = true;
     c->have_mesh = true;
     c->nclouds = C;
     c->nv = base + n;
@@ -1413,6 +1418,7 @@ int insert_clouds(dt_ctx *c, const double *xyz, uint64_t n, const std::vector<ui
         const int e = check_errors(c);
         if (e) rc = e;
     }
+    c->unfinished = rc != DT_OK;
     auto t2 = std::chrono::steady_clock::now();
     c->st.ms_sort += std::chrono::duration<double, std::milli>(t1 - t0).count();
     c->st.ms_insert += std::chrono::duration<double, std::milli>(t2 - t1).count();
@@ -1963,6 +1969,7 @@ int dt_clear(dt_ctx *c) {
     c->npoints = c->nv = 0;
     c->past_n = 0;
     c->have_mesh = false;
+    c->unfinished = false;
     c->mesh_vertices = 0;
     c->fl_idx = c->list_idx = c->ovf_idx = 0;
     c->st = dt_stats{};
