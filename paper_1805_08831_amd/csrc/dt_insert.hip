@@ -452,7 +452,7 @@ __device__ __forceinline__ void lane_fence() {
 //
 // Claims: every neighbour examined is tested first and then claimed once, with S if it is
 // inside (S is the attempt's stamp) and S + 1 if it is outside; settle_claim takes what the
-// claim found one step later, behind the next loads and tests.  The claims on tetrahedra
+// claim found one step later, behind the next loads and (filter pass) tests.  The claims on tetrahedra
 // outside are needed: without them an attempt that has lost runs on and displaces others
 // (measured: 8 % more rounds at 1e5 points; a plain load of the claim word in their place saved
 // 6 % of this kernel at 1e7 but then winners must read all the words of their cavities and
@@ -617,8 +617,10 @@ __global__ __launch_bounds__(256) void k_cavity_g(RoundArgs a) {
             lane_fence<GLOBAL>();
             // each step's claims are settled at the end of the next step (or after the last), so
             // that the atomics' latency overlaps that step's loads and tests (before its loads
-            // of vertices: 144.1 against 142.8 ms a pass at 1e7 points); the walk's tetrahedron
-            // is inside, its claim is settled with the first step's
+            // of vertices: 144.1 against 142.8 ms a pass at 1e7 points); with exact predicates
+            // they are settled before the tests, which a loser then does not make
+            // (181 points in a tetrahedron of scales from 1e-18 to 1e21: 158 against 130 ms); the
+            // walk's tetrahedron is inside, its claim is settled with the first step's
             bool pneed = gl == 0, pinside = true;
             unsigned long long po1 = ~0ull;
             if (gl == 0) {
@@ -653,6 +655,17 @@ __global__ __launch_bounds__(256) void k_cavity_g(RoundArgs a) {
                 if (lv) {
                     cv = T[c].v;
                     cn = T[c].n;
+                }
+                // the previous step's claims: with exact predicates before this step's tests, else
+                // behind them
+                bool beaten = false;
+                if (FULL) {
+                    beaten = pneed && settle_claim(a, S, pinside, po1);
+                    pneed = false;
+                    if (__ballot(beaten) & gmask) {
+                        status = ST_CONFLICT;
+                        break;
+                    }
                 }
                 const code ncode = comp(cn, f);
                 const uint32_t u = code_slot(ncode);
@@ -706,12 +719,13 @@ __global__ __launch_bounds__(256) void k_cavity_g(RoundArgs a) {
                         undecided = si == UNDECIDED;
                     }
                 }
-                // the previous step's claims
-                const bool beaten = pneed && settle_claim(a, S, pinside, po1);
-                pneed = false;
-                if (__ballot(beaten) & gmask) {
-                    status = ST_CONFLICT;
-                    break;
+                if (!FULL) {
+                    beaten = pneed && settle_claim(a, S, pinside, po1);
+                    pneed = false;
+                    if (__ballot(beaten) & gmask) {
+                        status = ST_CONFLICT;
+                        break;
+                    }
                 }
                 // a sign the filter could not decide: no claim on this step, the FULL kernel
                 // runs the attempt again
