@@ -1266,13 +1266,13 @@ int insert_clouds(dt_ctx *c, const double *xyz, uint64_t n, const std::vector<ui
     if ((rc = upload_levels(c, lv, &d_start, &d_size, &d_bits, &d_rb))) return rc;
     HIPCHK(launch_anchor(lord, d_start, L, c->V.p, base, n, c->anchor.p, c->stream));
     // an appended call finds its walk starts among the vertices of the largest earlier call; where
-    // the earlier points are at least half as many as the call's own, its walks start there at
-    // once, as those of refinement candidates at their tetrahedra.  Calls that all fill one box walk
-    // 6.75 steps a point instead of 8.97 so (6 calls of 50,000 points, 24.1 against 24.2 ms).  Calls
-    // that tile space instead (8 to 64 boxes or slabs side by side, boxes apart, boxes that double)
-    // take the same time with and without this rule, within the 5 to 25 % by which their passes
-    // differ: points beyond the hull have cavities that share its ghosts, 40 to 290 attempts of a
-    // point lose, and retries start where the last attempt ended
+    // the earlier points are at least half as many as the call's own, walks of the records that found
+    // one start there at once, as those of refinement candidates at their tetrahedra.  Calls that all
+    // fill one box walk 6.75 steps a point instead of 8.97 so (6 calls of 50,000 points, 24.1 against
+    // 24.2 ms).  Calls that tile space instead (8 to 64 boxes or slabs side by side, boxes apart, boxes
+    // that double) take the same time with and without this rule, within the 5 to 25 % by which
+    // their passes differ: points beyond the hull have cavities that share its ghosts, 40 to 290
+    // attempts of a point lose, and retries start where the last attempt ended
     if (!fresh && !hint && c->past_n)
         HIPCHK(launch_append_anchor(c->V.p, base, n, c->past.p, c->vtet.p, c->anchor.p, c->stream));
     c->near_anchor = hint || (!fresh && 2 * base >= n);

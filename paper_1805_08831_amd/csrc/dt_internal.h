@@ -165,7 +165,7 @@ struct RoundArgs {
     uint32_t walk_cap;           // filter pass: walk steps after which an attempt stops (ST_WALK)
     Cloud *clouds;               // the call's clouds (walk bounds, live tetrahedron)
     uint32_t *log_att;           // if set: attempts per record of the call (record - vlo)
-    uint32_t near_anchor;        // 1: walks start at the anchor (the mesh is denser than the call)
+    uint32_t near_anchor;        // 1: walks start at anchors before vlo (the mesh is denser there)
     const uint8_t *wbucket;      // if set: 1 = start the walk at the anchor (record - vlo)
     const uint32_t *cand_pt;     // current candidate list
     const uint32_t *cand_rank;

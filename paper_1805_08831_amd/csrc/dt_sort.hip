@@ -315,6 +315,13 @@ hipError_t launch_hint_anchor(const Vert *V, uint64_t base, uint64_t n, uint64_t
 // level has none: walks then cross the mesh from one known tetrahedron, stop at the walk cap and
 // go on in the next round (300,007 points in 6 calls: 77 walk steps a point and 41.2 ms a pass; 7 and
 // 29.3 ms with these anchors).
+// Where one cell holds more than half of the earlier call's records, the grid does not resolve
+// them: the four records are then any of the cell's, and on points whose scales spread over many
+// powers of two walks from there were long and exact (scales over 2^160, 2000 points and 400 more:
+// the second call 127 ms with such anchors, 14 without).  Records of that cell keep their own
+// anchors, in calls of 64 records and more.  (A limit of 64 records a cell instead: 200,000 points
+// of 20 clusters in 4 calls 28.0 against 24.7 ms.)
+constexpr uint32_t APPEND_HALF_MIN = 32;
 __global__ void k_append_anchor(const Vert *__restrict__ V, uint64_t base, uint64_t n, const Cloud *__restrict__ past,
                                 unsigned long long states, const uint32_t *__restrict__ vtet,
                                 uint32_t *__restrict__ anchor) {
@@ -341,6 +348,8 @@ __global__ void k_append_anchor(const Vert *__restrict__ V, uint64_t base, uint6
         const Vert b = V[r];
         return (a.x - b.x) * (a.x - b.x) + (a.y - b.y) * (a.y - b.y) + (a.z - b.z) * (a.z - b.z);
     };
+    const uint32_t half = (cl.hi - cl.lo) / 2;
+    if (half >= APPEND_HALF_MIN && half < cl.hi - lo && key(V[lo + half]) == mine) return;
     const uint32_t own = anchor[j];
     uint32_t at = own;
     double best = own != NONE ? dist(own) : INFINITY;

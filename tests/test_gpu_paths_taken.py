@@ -98,3 +98,21 @@ def test_hand_over_to_the_rounds_for_large_cavities(dtlib, oracle_mod, n, opts):
         t, nb = tri.tets()
     assert_parity(oracle_mod, xyz, t.astype(np.int64), f"{n} {opts}")
     check_invariants(xyz, t.astype(np.int64), nb, oracle_mod, expect_vertices=np.arange(len(xyz)))
+
+
+@pytest.mark.parametrize("seed", [0, 1, 2, 3])
+def test_appended_walks_on_spread_scales(dtlib, oracle_mod, seed):
+    """Points whose scales spread over 2^160: one cell of the first call's grid holds nearly all of
+    its records, and those around a point's place are no start for its walk.  Exact orientations,
+    most of the calls' time: 48,000 to 77,000 from the calls' own records, 139,000 to 431,000 from
+    there."""
+    say(f"append: spread scales, {seed}")
+    rng = np.random.default_rng(seed)
+    parts = [(rng.random((n, 3)) - 0.5) * 2.0 ** rng.integers(-60, 100, (n, 1)) for n in (1000, 500, 500, 500)]
+    with dtlib.Triangulation() as tri:
+        for p in parts:
+            tri.insert(p)
+        exact = tri.stats()["orient_exact"]
+        assert_parity(oracle_mod, np.vstack(parts), tri.tets()[0].astype(np.int64), f"spread scales {seed}")
+    say(f"append: {exact} exact orientations")
+    assert exact < 110_000
