@@ -202,6 +202,7 @@ struct dt_ctx {
     DevBuf<Cloud> past;
     uint64_t past_n = 0;                 // its points, 0: none
     bool near_anchor = false;            // of the current call: see RoundArgs
+    bool append_start = false;           // of the current call: wbucket holds the appended records' starts
     DevBuf<uint64_t> off, ch_start, ch_end;
     DevBuf<uint32_t> cloud_ch;
     DevBuf<double> partial;
@@ -572,7 +573,7 @@ int enqueue_round(dt_ctx *c, int ci, int ni, int oi, uint32_t max_cand, uint32_t
     a.walk_cap = c->opt.walk_cap ? c->opt.walk_cap : DEFAULT_WALK_CAP;
     a.clouds = c->clouds.p;
     a.log_att = c->logged ? c->log_att.p : nullptr;
-    a.wbucket = c->learned_active ? c->wbucket.p : nullptr;
+    a.wbucket = c->learned_active || c->append_start ? c->wbucket.p : nullptr;
     a.near_anchor = c->near_anchor ? 1u : 0u;
     a.cand_pt = c->lpt[ci] + off;
     a.cand_rank = c->lrank[ci] + off;
@@ -1266,16 +1267,23 @@ int insert_clouds(dt_ctx *c, const double *xyz, uint64_t n, const std::vector<ui
     if ((rc = upload_levels(c, lv, &d_start, &d_size, &d_bits, &d_rb))) return rc;
     HIPCHK(launch_anchor(lord, d_start, L, c->V.p, base, n, c->anchor.p, c->stream));
     // an appended call finds its walk starts among the vertices of the largest earlier call; where
-    // the earlier points are at least half as many as the call's own, walks of the records that found
-    // one start there at once, as those of refinement candidates at their tetrahedra.  Calls that all
-    // fill one box walk 6.75 steps a point instead of 8.97 so (6 calls of 50,000 points, 24.1 against
-    // 24.2 ms).  Calls that tile space instead (8 to 64 boxes or slabs side by side, boxes apart, boxes
-    // that double) take the same time with and without this rule, within the 5 to 25 % by which
-    // their passes differ: points beyond the hull have cavities that share its ghosts, 40 to 290
-    // attempts of a point lose, and retries start where the last attempt ended
-    if (!fresh && !hint && c->past_n)
-        HIPCHK(launch_append_anchor(c->V.p, base, n, c->past.p, c->vtet.p, c->anchor.p, c->stream));
-    c->near_anchor = hint || (!fresh && 2 * base >= n);
+    // the earlier points are at least half as many as the call's own, walks of the records inside
+    // that call's grid start there at once, as those of refinement candidates at their
+    // tetrahedra.  300,007 points in 6 calls walk 7.0 steps a point so and 9.2 if curve neighbours come
+    // first, 25.3 and 25.5 ms; 200,000 points of 20 clusters in 4 calls 21.5 and 28.8, 24.5 and 25.8 ms.
+    // Beyond the grid an anchor is a record of its border: 942 points of scales over 2^160 after 1419
+    // inside a box of size 6, 1.9 s if they start there at once, 0.8 if not.  Calls that tile space (8
+    // to 64 boxes or slabs side by side, boxes apart, boxes that double) take the same time with and
+    // without this rule, within the 5 to 25 % by which their passes differ: points beyond the hull
+    // have cavities that share its ghosts, 40 to 290 attempts of a point lose, and retries start where
+    // the last attempt ended
+    c->append_start = !fresh && !hint && c->past_n && 2 * base >= n;
+    if (!fresh && !hint && c->past_n) {
+        if (c->append_start && (rc = ensure(c, c->wbucket, n))) return rc;
+        HIPCHK(launch_append_anchor(c->V.p, base, n, c->past.p, c->vtet.p, c->anchor.p,
+                                    c->append_start ? c->wbucket.p : nullptr, c->stream));
+    }
+    c->near_anchor = hint != nullptr;
     if (hint) HIPCHK(launch_hint_anchor(c->V.p, base, n, c->npoints, hint, c->anchor.p, c->stream));
     HIPCHK(hipMemsetAsync(c->lastt.p, 0xFF, n * sizeof(uint32_t), c->stream));
     c->call_clouds = C;

@@ -513,9 +513,9 @@ __global__ __launch_bounds__(256) void k_cavity_g(RoundArgs a) {
         const uint32_t tl = a.lastt[p - a.vlo];
         const unsigned long long hm = __ballot(ht != NONE) & gmask;
         uint32_t t = hm ? __shfl(ht, __ffsll((long long)hm) - 1) : tq;
-        // the anchor is the closer start where it is a record of an older, denser mesh, or where
-        // the learned scheduler predicts it
-        if (tq != NONE && ((a.near_anchor && q < a.vlo) || (a.wbucket && a.wbucket[p - a.vlo]))) t = tq;
+        // the anchor is the closer start for refinement candidates, and for records of which an
+        // appended call or the learned scheduler says so
+        if (tq != NONE && (a.near_anchor || (a.wbucket && a.wbucket[p - a.vlo]))) t = tq;
         if (t == NONE) t = cl->any_live;
         // a retry starts where the last attempt located p: that tetrahedron, or the one the
         // ball of a winner built in its slot, is near p unless the slot went to another
@@ -848,7 +848,7 @@ __global__ __launch_bounds__(256) void k_cavity_b(RoundArgs a) {
     const uint32_t tl = a.lastt[p - a.vlo];
     const unsigned long long hmask = __ballot(ht != NONE);
     uint32_t t = hmask ? __shfl(ht, __ffsll((long long)hmask) - 1) : tq;
-    if (tq != NONE && ((a.near_anchor && q < a.vlo) || (a.wbucket && a.wbucket[p - a.vlo]))) t = tq;
+    if (tq != NONE && (a.near_anchor || (a.wbucket && a.wbucket[p - a.vlo]))) t = tq;
     if (t == NONE) t = cl->any_live;
     uint4 w;
     bool from_last = false;

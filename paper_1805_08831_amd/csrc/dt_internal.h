@@ -165,7 +165,7 @@ struct RoundArgs {
     uint32_t walk_cap;           // filter pass: walk steps after which an attempt stops (ST_WALK)
     Cloud *clouds;               // the call's clouds (walk bounds, live tetrahedron)
     uint32_t *log_att;           // if set: attempts per record of the call (record - vlo)
-    uint32_t near_anchor;        // 1: walks start at anchors before vlo (the mesh is denser there)
+    uint32_t near_anchor;        // 1: walks start at the anchor
     const uint8_t *wbucket;      // if set: 1 = start the walk at the anchor (record - vlo)
     const uint32_t *cand_pt;     // current candidate list
     const uint32_t *cand_rank;
@@ -243,7 +243,7 @@ hipError_t launch_levels(const uint32_t *src, const Vert *V, uint64_t n, uint64_
 hipError_t launch_hint_anchor(const Vert *V, uint64_t base, uint64_t n, uint64_t idx_offset, const uint32_t *hint,
                               uint32_t *anchor, hipStream_t s);
 hipError_t launch_append_anchor(const Vert *V, uint64_t base, uint64_t n, const Cloud *past, const uint32_t *vtet,
-                                uint32_t *anchor, hipStream_t s);
+                                uint32_t *anchor, uint8_t *start, hipStream_t s);
 hipError_t launch_anchor(const uint32_t *lord, const uint32_t *start, int L, const Vert *V, uint64_t base,
                          uint64_t n, uint32_t *anchor, hipStream_t s);
 hipError_t launch_dedupe(const Vert *V, uint64_t base, uint64_t n, unsigned long long *table,

@@ -322,9 +322,10 @@ hipError_t launch_hint_anchor(const Vert *V, uint64_t base, uint64_t n, uint64_t
 // anchors, in calls of 64 records and more.  (A limit of 64 records a cell instead: 200,000 points
 // of 20 clusters in 4 calls 28.0 against 24.7 ms.)
 constexpr uint32_t APPEND_HALF_MIN = 32;
+// start (may be null): 1 for records inside the grid whose anchor is the nearest of all these.
 __global__ void k_append_anchor(const Vert *__restrict__ V, uint64_t base, uint64_t n, const Cloud *__restrict__ past,
                                 unsigned long long states, const uint32_t *__restrict__ vtet,
-                                uint32_t *__restrict__ anchor) {
+                                uint32_t *__restrict__ anchor, uint8_t *__restrict__ start) {
     const uint64_t j = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x;
     if (j >= n) return;
     const Cloud cl = *past;
@@ -338,6 +339,7 @@ __global__ void k_append_anchor(const Vert *__restrict__ V, uint64_t base, uint6
     };
     const Vert a = V[base + j];
     const unsigned long long mine = key(a);
+    if (start) start[j] = 0;
     uint32_t lo = cl.lo, hi = cl.hi;
     while (lo < hi) {
         const uint32_t mid = lo + (hi - lo) / 2;
@@ -363,14 +365,19 @@ __global__ void k_append_anchor(const Vert *__restrict__ V, uint64_t base, uint6
         }
     }
     if (at != own) anchor[j] = at;
+    // inside the grid, or within a cell of it
+    const double g[3] = {(a.x - cl.box[0]) * cl.box[3], (a.y - cl.box[1]) * cl.box[3], (a.z - cl.box[2]) * cl.box[3]};
+    bool inside = true;
+    for (int k = 0; k < 3; ++k) inside = inside && g[k] >= -1.0 && g[k] < top + 2.0;
+    if (start) start[j] = inside ? 1 : 0;
 }
 
 hipError_t launch_append_anchor(const Vert *V, uint64_t base, uint64_t n, const Cloud *past, const uint32_t *vtet,
-                                uint32_t *anchor, hipStream_t s) {
+                                uint32_t *anchor, uint8_t *start, hipStream_t s) {
     const unsigned long long st = moore_states();
     if (!st) return hipErrorUnknown;
     if (n == 0) return hipSuccess;
-    k_append_anchor<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(V, base, n, past, st, vtet, anchor);
+    k_append_anchor<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(V, base, n, past, st, vtet, anchor, start);
     return hipGetLastError();
 }
 

@@ -117,3 +117,22 @@ def test_appended_walks_on_spread_scales(dtlib, oracle_mod, seed):
         assert_parity(oracle_mod, np.vstack(parts), tri.tets()[0].astype(np.int64), f"spread scales {seed}")
     say(f"append: {exact} exact orientations")
     assert exact < 110_000
+
+
+@pytest.mark.parametrize("seed", [0, 1, 2])
+def test_appended_walks_beyond_the_grid(dtlib, oracle_mod, seed):
+    """Points far beyond the earlier call's grid: records of its border, here nearly all on one line,
+    are no start for them where a curve neighbour is inserted.  Exact orientations: 134,000 to
+    151,000 with walks that start at the neighbour, 187,000 to 218,000 with walks from the border."""
+    say(f"append: beyond the grid, {seed}")
+    rng = np.random.default_rng(seed)
+    line = np.outer(rng.random(1300), [1.0, 2.0, 3.0])
+    line[:130] = rng.random((130, 3))
+    parts = [line] + [(rng.random((n, 3)) - 0.5) * 2.0 ** rng.integers(-60, 100, (n, 1)) for n in (100, 900)]
+    with dtlib.Triangulation() as tri:
+        for p in parts:
+            tri.insert(p)
+        exact = tri.stats()["orient_exact"]
+        assert_parity(oracle_mod, np.vstack(parts), tri.tets()[0].astype(np.int64), f"beyond the grid {seed}")
+    say(f"append: beyond the grid: {exact} exact orientations")
+    assert exact < 170_000
