@@ -60,8 +60,7 @@ typedef struct {
     uint32_t max_rounds;    /* 0: unlimited; otherwise DT_E_INCOMPLETE beyond it.  A new mesh's
                                first insertions (up to 576 vertices a cloud) run in one
                                launch that is no round, but as rounds when this,
-                               round_size, timing 1 or a cavity_cap below 48 is given, or
-                               for many clouds                                            */
+                               round_size or timing 1 is given, or for many clouds        */
     int timing;             /* 1: time the two insertion kernels of every round with HIP
                                events (three per round; the second interval holds the
                                selection of the winners, the DelaunayBall kernel and the

@@ -1382,16 +1382,13 @@ int insert_clouds(dt_ctx *c, const double *xyz, uint64_t n, const std::vector<ui
         c->log_n = n;
     }
     // the first insertions of a new mesh in one block per cloud.  Not under options that speak of
-    // rounds: a limit or a size of rounds, or every round timed.  Not below a capacity of cavities
-    // smaller than the blocks', which puts off the points with larger ones (a limit of 8, 10,306 points
-    // of which nine in ten lie on a line: 5.5 s with the blocks, 2.0 without).  Not for many clouds, whose first
+    // rounds: a limit or a size of rounds, or every round timed.  Not for many clouds, whose first
     // rounds fill the chip by themselves while their blocks, one to a compute unit, queue up
     // (with against without: clouds of 200 points, 256 of them 1.8 against 5.4 ms a call, 1024 4.6
     // against 7.5, 4096 16.4 against 12.5; of 2000 points, 1024 26.1 against 30.8, 4096 85.6 against
     // 83.0; of 30 points, 1024 1.8 against 2.4, 2048 2.8 against 2.5), nor for more than a few tiny
     // ones, done in a few rounds (of 8 points, 64 0.37 against 0.39, 256 0.77 against 0.49).
     const bool seed = fresh && c->opt.max_rounds == 0 && c->opt.round_size == 0 && c->opt.timing != 1 &&
-                      c->capC >= SEED_CAVITY_CAP &&
                       (C <= SEED_FEW_CLOUDS || (C <= SEED_MAX_CLOUDS && n >= (uint64_t)SEED_MEAN_POINTS * C));
     if (seed)
         HIPCHK(launch_seed(c->V.p, c->clouds.p, C, 0, c->lord + lv.start[0], lv.size[0], c->dup.p, c->T, c->wide,

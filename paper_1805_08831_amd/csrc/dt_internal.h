@@ -289,8 +289,6 @@ hipError_t launch_init(const Vert *V, Cloud *clouds, uint32_t nclouds, uint32_t 
                        void *T, bool wide, uint32_t *vtet, Ctr *ctr, void *subd, hipStream_t s);
 // the first insertions of each cloud of a fresh call in one block's LDS (dt_seed.hip); lord,
 // nlord: the first level's records.  Counts its insertions in ctr->won.
-// SEED_CAVITY_CAP: cavity tetrahedra that it holds per insertion.
-constexpr uint32_t SEED_CAVITY_CAP = 48;
 hipError_t launch_seed(const Vert *V, Cloud *clouds, uint32_t nclouds, uint32_t first_slot, const uint32_t *lord,
                        uint32_t nlord, const uint8_t *dup, void *T, bool wide, uint32_t tcap, uint32_t *vtet,
                        Ctr *ctr, void *subd, unsigned long long *stat, uint32_t *log_att, uint32_t vlo,

@@ -33,7 +33,7 @@ constexpr int SEED_GROUPS = SEED_THREADS / SEED_LANES;
 // LDS: 34 bytes per vertex, 20 per tetrahedron and 480 per group, 112 KB in all
 constexpr uint32_t SEED_VERTS = 576;
 constexpr uint32_t SEED_TETS = 4224;  // uniform clouds have about 6.6 per vertex at this size
-constexpr uint32_t SEED_CAV = SEED_CAVITY_CAP, SEED_BND = 64;
+constexpr uint32_t SEED_CAV = 48, SEED_BND = 64;
 constexpr uint32_t SEED_ROUNDS = 8 * SEED_VERTS;  // far more than a run takes
 constexpr uint32_t SEED_WALK = 64;  // steps of a walk in one round; it goes on in the next
 

@@ -33,8 +33,7 @@ SEEDED = 12
 
 @pytest.mark.parametrize("opts,seeded", [
     ({}, True), (dict(index_bits=64), True), (dict(timing=2), True), (dict(timing=1), False),
-    (dict(round_size=4096), False), (dict(max_rounds=100000), False), (dict(cavity_cap=48), True),
-    (dict(cavity_cap=47), False), (dict(cavity_cap=8), False)])
+    (dict(round_size=4096), False), (dict(max_rounds=100000), False)])
 def test_first_insertions_run(dtlib, oracle_mod, opts, seeded):
     say(f"first insertions: {opts}")
     st = mesh(dtlib, oracle_mod, [uniform_points(576, 951)], **opts)
