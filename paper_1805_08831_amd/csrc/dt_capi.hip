@@ -51,6 +51,8 @@ constexpr uint32_t ROUND_MIN = 256;
 constexpr uint32_t SEED_FEW_CLOUDS = 64, SEED_MAX_CLOUDS = 1024, SEED_MEAN_POINTS = 16;
 constexpr uint32_t DRAIN_SLICE = 4096;  // candidates per round when draining overflowed cavities
 constexpr uint32_t EXPORT_CHUNK = 1u << 24;  // slots per staged export launch (a multiple of 64)
+// three snapshots of the counters, their tags and the balls' error word
+constexpr size_t RING_BYTES = 3 * sizeof(Ctr) + 4 * sizeof(unsigned long long);
 constexpr size_t TET_BYTES = 64;               // one tetrahedron record, either layout
 constexpr size_t SUBD_BYTES = 40;              // its cached sub-determinants (dt_options.subdet_cache)
 // entries of each free list: slots freed while it is full stay unused (the pool has room for
@@ -166,6 +168,7 @@ struct dt_ctx {
     // to the round's tag (else a copy and an event per round)
     bool ring_direct = false;
     unsigned long long *hseq = nullptr;
+    uint32_t *herror = nullptr;  // pinned, behind the ring: errors of the call's balls
     unsigned long long tag_counter = 0;
     unsigned long long slot_tag[3] = {0, 0, 0};
     unsigned long long *stat = nullptr;  // spread work statistics (summed into ctr each round)
@@ -603,6 +606,7 @@ int enqueue_round(dt_ctx *c, int ci, int ni, int oi, uint32_t max_cand, uint32_t
     a.fl_next = c->fl[c->fl_idx ^ 1];
     a.flcap = c->flcap;
     a.ctr = d;
+    a.host_error = c->herror;
     a.stat = c->stat;
     a.stride = std::max<uint32_t>(max_cand, 1);
     a.capC = capC;
@@ -668,7 +672,7 @@ int enqueue_round(dt_ctx *c, int ci, int ni, int oi, uint32_t max_cand, uint32_t
         c->fl_idx ^= 1;
         HIPCHK(launch_round_graph(c->graphs, plan ? *plan : none, fa ? *fa : nofill, a, c->wide, max_cand, lanes, end,
                                   c->stream));
-        if (raise_behind) HIPCHK(launch_error_bits(d, raise_behind, 0, nullptr, c->stream));
+        if (raise_behind) HIPCHK(launch_error_bits(d, raise_behind, 0, c->herror, c->stream));
         c->slot_cand[slot] = max_cand;
         c->slot_capC[slot] = capC;
         c->st.rounds++;
@@ -681,7 +685,7 @@ int enqueue_round(dt_ctx *c, int ci, int ni, int oi, uint32_t max_cand, uint32_t
                                 fa->vtet, fa->cand_pt, fa->cand_rank, fa->ncand, c->stream));
     HIPCHK(launch_round(a, c->wide, max_cand, lanes, c->large_lanes, c->exact_needed, end, c->stream,
                         timed ? evs : nullptr));
-    if (raise_behind) HIPCHK(launch_error_bits(d, raise_behind, 0, nullptr, c->stream));
+    if (raise_behind) HIPCHK(launch_error_bits(d, raise_behind, 0, c->herror, c->stream));
     c->fl_idx ^= 1;
     if (!c->ring_direct) {
         HIPCHK(hipMemcpyAsync(&c->hring[slot], c->ctr, sizeof(Ctr), hipMemcpyDeviceToHost, c->stream));
@@ -1387,7 +1391,10 @@ int insert_clouds(dt_ctx *c, const double *xyz, uint64_t n, const std::vector<ui
     // (with against without: clouds of 200 points, 256 of them 1.8 against 5.4 ms a call, 1024 4.6
     // against 7.5, 4096 16.4 against 12.5; of 2000 points, 1024 26.1 against 30.8, 4096 85.6 against
     // 83.0; of 30 points, 1024 1.8 against 2.4, 2048 2.8 against 2.5), nor for more than a few tiny
-    // ones, done in a few rounds (of 8 points, 64 0.37 against 0.39, 256 0.77 against 0.49).
+    // ones, done in a few rounds (of 8 points, 64 0.37 against 0.39, 256 0.77 against 0.49).  A small
+    // capacity of cavities (the default is 128) does not speak against them: with 12, 200,000 uniform
+    // points take 0.21 s and 2.35 s without them, since nearly every early insertion then overflows;
+    // with 8, 10,306 points of which nine in ten lie on a line take 5.5 s and 2.0 without.
     const bool seed = fresh && c->opt.max_rounds == 0 && c->opt.round_size == 0 && c->opt.timing != 1 &&
                       (C <= SEED_FEW_CLOUDS || (C <= SEED_MAX_CLOUDS && n >= (uint64_t)SEED_MEAN_POINTS * C));
     if (seed)
@@ -1408,6 +1415,7 @@ int insert_clouds(dt_ctx *c, const double *xyz, uint64_t n, const std::vector<ui
     auto t1 = std::chrono::steady_clock::now();
     // 8. insertion rounds
     c->unfinished = true;
+    if (c->herror) *c->herror = 0;
     c->have_mesh = true;
     c->nclouds = C;
     c->nv = base + n;
@@ -1417,12 +1425,11 @@ int insert_clouds(dt_ctx *c, const double *xyz, uint64_t n, const std::vector<ui
     if ((rc = ensure_round_buffers(c, (uint32_t)std::min<uint64_t>(want_r, std::max<uint64_t>(n, ROUND_MIN)))))
         return rc;
     rc = run_rounds(c, lv, d_start, d_size, d_bits, d_rb, base, n);
-    // a round's balls are built behind the snapshot that its round end writes, and what they raise is
-    // in the next round's: after the last round the error word is read once more (snapshots that are
-    // copies are taken behind the balls)
+    // the last round's balls are built behind the snapshot that its round end writes: errors that they
+    // raise are in the balls' own word (snapshots that are copies are taken behind the balls)
     if (c->ring_direct && (rc == DT_OK || rc == DT_E_INCOMPLETE)) {
-        HIPCHK(launch_error_bits(c->ctr, 0, 0, &c->hctr->error, c->stream));
         HIPCHK(hipStreamSynchronize(c->stream));
+        c->hctr->error |= *c->herror;
         const int e = check_errors(c);
         if (e) rc = e;
     }
@@ -1482,12 +1489,12 @@ int dt_create(dt_ctx **out, const dt_options *opt) {
     apply_options(c);
     if (!rc && (hipMalloc((void **)&c->ctr, sizeof(Ctr)) != hipSuccess ||
                 hipMalloc((void **)&c->stat, STAT_WORDS * sizeof(unsigned long long)) != hipSuccess ||
-                hipHostMalloc((void **)&c->hring, 3 * sizeof(Ctr) + 3 * sizeof(unsigned long long),
-                              hipHostMallocDefault) != hipSuccess))
+                hipHostMalloc((void **)&c->hring, RING_BYTES, hipHostMallocDefault) != hipSuccess))
         rc = DT_E_DEVICE;
     if (!rc) {
         c->hctr = c->hring;
         c->hseq = reinterpret_cast<unsigned long long *>(c->hring + 3);
+        c->herror = reinterpret_cast<uint32_t *>(c->hseq + 3);
         c->ring_direct = true;
     }
     for (int k = 0; k < 3 && !rc; ++k) {
@@ -1504,7 +1511,7 @@ int dt_create(dt_ctx **out, const dt_options *opt) {
         dt_destroy(c);
         return rc;
     }
-    std::memset(c->hring, 0, 3 * sizeof(Ctr) + 3 * sizeof(unsigned long long));
+    std::memset(c->hring, 0, RING_BYTES);
     *out = c;
     return DT_OK;
 }

@@ -1374,6 +1374,12 @@ __device__ __forceinline__ unsigned long long facet_edge(const uint32_t wv[4], i
     return e0 < e1 ? ((unsigned long long)e0 << 32) | e1 : ((unsigned long long)e1 << 32) | e0;
 }
 
+// An error of a ball: for the next snapshot, and at once for the host, which has this round's
+__device__ __forceinline__ void ball_error(const RoundArgs &a) {
+    atomicOr(&a.ctr->error, ERR_WALK);
+    if (a.host_error) *a.host_error = ERR_WALK;
+}
+
 template <class K, int GL, int BS>
 __global__ __launch_bounds__(BS) void k_ball(RoundArgs a) {
     using code = typename K::code;
@@ -1470,7 +1476,7 @@ __global__ __launch_bounds__(BS) void k_ball(RoundArgs a) {
                             h = (h + 1) & (HT - 1);
                         }
                     }
-                    if (!placed) atomicOr(&a.ctr->error, ERR_WALK);
+                    if (!placed) ball_error(a);
                 }
             }
         }
@@ -1494,7 +1500,7 @@ __global__ __launch_bounds__(BS) void k_ball(RoundArgs a) {
                         const uint32_t v0 = s_val[gi][h][0], v1 = s_val[gi][h][1];
                         uint32_t res = v0 == mine ? v1 : v0;
                         if ((res >> 2) >= nb) {  // an edge on one facet only: never expected
-                            atomicOr(&a.ctr->error, ERR_WALK);
+                            ball_error(a);
                             res = mine;
                         }
                         c = make_code<K>(s_slot[gi][res >> 2], res & 3u);
@@ -1607,7 +1613,7 @@ __global__ __launch_bounds__(BS) void k_ball(RoundArgs a) {
                 f = code_facet(lc);
                 if (k >= nc) break;
             }
-            if (!found) atomicOr(&a.ctr->error, ERR_WALK);
+            if (!found) ball_error(a);
             else nref(T, slot, q) = res;
         }
     }
@@ -1824,12 +1830,11 @@ hipError_t launch_reset_claims(void *T, bool wide, uint32_t tcap, hipStream_t s)
     return hipGetLastError();
 }
 
-// Sets and clears bits of the counters' error word, behind whatever the stream holds; the result
-// also goes to `out` (pinned host memory, may be null): a launch takes less than a copy.
+// Sets and clears bits of the counters' error word, behind whatever the stream holds; the bits set
+// also go to `out` (pinned host memory, may be null).
 __global__ void k_error_bits(Ctr *__restrict__ ctr, uint32_t set, uint32_t clear, uint32_t *__restrict__ out) {
-    const uint32_t e = (ctr->error | set) & ~clear;
-    ctr->error = e;
-    if (out) *out = e;
+    ctr->error = (ctr->error | set) & ~clear;
+    if (out) *out = set;
 }
 
 hipError_t launch_error_bits(Ctr *ctr, uint32_t set, uint32_t clear, uint32_t *out, hipStream_t s) {

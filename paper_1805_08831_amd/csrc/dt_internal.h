@@ -193,6 +193,7 @@ struct RoundArgs {
     uint32_t *fl_next;           // free list filled this round
     uint32_t flcap;              // entries of each free list (slots freed beyond it are dropped)
     Ctr *ctr;
+    uint32_t *host_error;        // pinned: errors of balls, whose round's snapshot is written before them
     unsigned long long *stat;    // [NSTAT][STAT_SPREAD][STAT_PAD] work statistics
     uint32_t stride, capC, capF, tcap;
     uint32_t hmg;                // capC > 1024: entries of the cavity set in global memory
@@ -308,7 +309,7 @@ struct RoundEnd {
 };
 // The kernels of a round: cavity passes, selection, round end (the host's copy of the counters is
 // written before the balls are built, so that it plans on while they are; errors that the balls
-// raise are in the next copy), DelaunayBall.
+// raise go to a word of their own too), DelaunayBall.
 // exact: launch the exact-predicate pass after the filter pass of a regular round (without
 // it, attempts the filter hands on retry in the next round)
 hipError_t launch_round(const RoundArgs &a, bool wide, uint32_t max_cand, uint32_t lanes, uint32_t large_lanes,
